@@ -12,7 +12,10 @@
  * sign (a) and disagree (b), and add C(a,2) + C(b,2).  Only pairs of agreeing
  * or pairs of disagreeing wedges close a balanced butterfly (Lemma 1), so no
  * unbalanced structure is ever formed.  Ranks follow the vertex priority of
- * Definition 6 (degree, then id).  Every step runs in the library's own HIP
+ * Definition 6 (degree, then id).  Totals without dense blocks or per-vertex
+ * output are counted from both sides where that walks fewer wedges: each
+ * butterfly at its vertex of highest degree (class), from the wedges whose
+ * middle and end lie below that vertex; the count is the same.  Every step runs in the library's own HIP
  * kernels on the caller's stream; counts are exact integers.
  *
  * Entry points: bbc_count (total, optional per-vertex counts and dense
@@ -107,7 +110,7 @@ typedef struct {
     int32_t side;         /* BBC_SIDE_* */
     uint32_t checks;      /* BBC_CHECK_* mask, default BBC_CHECK_ALL */
     int32_t timing;       /* nonzero: record per-phase HIP event times (bbc_last_stats) */
-    int32_t band_words;   /* LDS counter band in 32-bit words per workgroup, 0 = default */
+    int32_t band_words;   /* LDS counter band in 32-bit words per workgroup, 0 = default (totals: by the graph's size) */
     int32_t wg_size;      /* threads per wedge-kernel workgroup, 0 = default */
     int32_t wg_per_cu;    /* persistent workgroups per compute unit, 0 = as many as fit */
     /* Dense-block hybrid (bbc_count only, no per-vertex output).  For the
@@ -262,7 +265,8 @@ typedef struct {
     int32_t n_anchor;     /* vertices on the anchor side */
     int32_t n_centre;     /* vertices on the other side */
     int64_t n_edges;
-    uint64_t wedges;      /* sum over centres c of C(deg c, 2): wedges walked once each */
+    uint64_t wedges;      /* sum over centres c of C(deg c, 2): the wedges of the anchor side (a count from both
+                           * sides walks fewer) */
     uint64_t bands;       /* LDS counter bands processed by the wedge kernel */
     int32_t grid;         /* persistent workgroups launched */
     int32_t block;        /* threads per workgroup */

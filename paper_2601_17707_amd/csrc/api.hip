@@ -13,6 +13,7 @@
 
 #include "../../include/bbc.h"
 #include "bbc_internal.h"
+#include "top.h"
 
 namespace bbc {
 void launch_decode_single(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v,
@@ -99,7 +100,10 @@ int wedge_light_max(int band_words, int wg);
 int wedge_bic_blocks_per_cu();
 void launch_choose_table(int32_t k, unsigned long long* tab, hipStream_t s);
 
-__global__ void k_status_init(DevStatus* st) {
+constexpr int kStatusThreads = 512;
+__global__ __launch_bounds__(kStatusThreads) void k_status_init(DevStatus* st) {
+    unsigned long long* w = reinterpret_cast<unsigned long long*>(st->sums);
+    for (int i = threadIdx.x; i < kSumSlots * (int)sizeof(DevSums) / 8; i += kStatusThreads) w[i] = 0;
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         st->flags = 0;
         st->bad_offset = st->bad_range = st->bad_sign = st->bad_dup = st->bad_block = st->bad_update = INT64_MAX;
@@ -264,7 +268,22 @@ struct Job {
     int64_t r_first = 0;  // first rank of the block anchors (they sit at the top)
     int64_t max_ids = 0, mat_bytes = 0, tab_words = 0;
     uint64_t dense_ops = 0;
+    // top-vertex pipeline (totals without dense blocks; see top.h)
+    bool top = false;
+    int top_words = 0, top_wg = 0, top_grid = 0, light_grid = 0, n_cu = 0;
 };
+
+// Whether the job takes the top-vertex pipeline: positions of both sides'
+// lists (2 m) must fit 30 bits, and neither side may be more than kTopRatio
+// times the other (a small side of hubs over a large side of low degrees
+// leaves nothing for the order to save, and its hubs' middles are all short
+// lists: 102 ms against 16 ms for the one-sided walk on 2.5M x 100K vertices
+// and 100M edges).
+constexpr int64_t kTopRatio = 8;
+bool top_fits(const Job& J) {
+    return J.m > 0 && J.m <= (1ll << 29) && J.n_u >= 1 && J.n_v >= 1 && J.n_u <= kTopRatio * J.n_v &&
+           J.n_v <= kTopRatio * J.n_u;
+}
 
 // All device buffers of one pass, carved from an arena in a fixed order.
 struct Plan {
@@ -354,6 +373,112 @@ struct Plan {
     }
 };
 
+// Device buffers of one top-vertex pass.
+struct TopPlan {
+    TopBuild t;
+    uint32_t *hist, *hist_scan, *partials;
+    size_t carve(char* base, const Job& J) {
+        Carve c(base);
+        const int64_t m = J.m, nu = J.n_u, nv = J.n_v, n = nu + nv;
+        t.tc = c.take<TopCounts>(1);
+        t.deg = c.take<uint32_t>(n);
+        t.key = c.take<uint32_t>(n);
+        t.inv = c.take<uint32_t>(n);
+        t.vk_a = c.take<uint32_t>(n);
+        t.vv_a = c.take<uint32_t>(n);
+        t.rank = c.take<int32_t>(n);
+        t.degr = c.take<uint32_t>(n);
+        t.off = c.take<uint32_t>(n + 1);
+        t.thr = c.take<uint32_t>(n);
+        t.kx = c.take<uint32_t>(n);
+        t.order = c.take<uint32_t>(n);
+        t.skey = c.take<uint32_t>(n);
+        t.first = c.take<uint32_t>(nv);
+        t.last = c.take<uint32_t>(nv);
+        t.work = c.take<unsigned long long>(n);
+        t.cstart = c.take<uint32_t>(2 * (kDegClasses + 1));
+        t.bands = c.take<TopBands>(2);
+        t.ent = c.take<uint32_t>(2 * m);
+        t.cross = c.take<uint32_t>(2 * m);
+        t.mstart = c.take<uint32_t>(2 * m);
+        t.e = c.take<uint32_t>(6 * m);
+        t.icnt = c.take<uint32_t>(n);
+        t.ioff = c.take<uint32_t>(n + 1);
+        t.idx = c.take<uint32_t>(2 * m + (kTopFewBands + 1) * n);
+        const int64_t hs = (int64_t)radix_hist_size(std::max(m, n));
+        hist = c.take<uint32_t>(hs);
+        hist_scan = c.take<uint32_t>(hs + 1);
+        partials = c.take<uint32_t>((int64_t)scan_partials_size(std::max<int64_t>(hs, n + 1) + 8));
+        return c.used;
+    }
+};
+
+// Ranks one side: ids in (class, id) order, then ranks, degrees by rank and
+// class starts.
+void top_rank_side(TopPlan& P, int64_t n, int side, int64_t x0, hipStream_t s) {
+    TopBuild& T = P.t;
+    radix_sort_to(T.key, SortBufs{}, SortBufs{}, nullptr, nullptr, true, 0u, SortBufs{T.vk_a, nullptr, T.vv_a}, nullptr,
+                  n, 0, 8, P.hist, P.hist_scan, P.partials, s);
+    top_ranks(T.vv_a, T.deg, n, side, T.rank, T.degr + x0, T.cstart, s);
+}
+
+// Queues the top-vertex pipeline on stream s (kernel launches only).
+void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEvent_t* ev) {
+    TopBuild& T = P.t;
+    const int64_t m = J.m, nu = J.n_u, nv = J.n_v, n = nu + nv;
+    const int check_sign = (J.checks & BBC_CHECK_SIGNS) ? 1 : 0;
+    const int check_dup = (J.checks & BBC_CHECK_DUPLICATES) ? 1 : 0;
+    uint32_t* e[6];
+    for (int i = 0; i < 6; ++i) e[i] = T.e + i * m;
+    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, st);
+    fill_u32(reinterpret_cast<uint32_t*>(T.tc), 0u, sizeof(TopCounts) / 4, s);
+    // U ranks come from the offsets; the decode moves the rows to rank order
+    top_vertex_u(J.off, (int32_t)nu, m, T.deg, T.key, st, s);
+    top_rank_side(P, nu, 0, 0, s);
+    scan_exclusive_u32(T.degr, T.off, nu, P.partials, s);
+    top_decode(J.off, J.adj, J.sg, (int32_t)nu, (int32_t)nv, m, check_sign, T.rank, T.off, st, e[0], e[1], s);
+    if (ev) (void)hipEventRecord(ev[0], s);
+
+    // V lists: stable by V id, then to rank order
+    const int bits_v = bits_for((uint64_t)(nv - 1)), bits_u = bits_for((uint64_t)(nu - 1));
+    const bool odd1 = m <= 4096 || (radix_passes(bits_v) & 1);
+    uint32_t *sk = odd1 ? e[2] : e[0], *sp = odd1 ? e[3] : e[1];
+    radix_sort_to(e[0], SortBufs{e[2], e[3], nullptr}, SortBufs{e[0], e[1], nullptr}, e[1], nullptr, false, 0u,
+                  SortBufs{sk, sp, nullptr}, nullptr, m, 0, bits_v, P.hist, P.hist_scan, P.partials, s);
+    top_runs(sk, sp, m, nv, check_dup, T.first, T.last, T.deg, T.key, st, s);
+    top_rank_side(P, nv, 1, nu, s);
+    scan_exclusive_u32(T.degr + nu, T.off + nu, nv, P.partials, s, (uint32_t)m);
+    top_move(sk, sp, m, T.first, T.rank, T.off + nu, T.ent + m, e[4], st, s);
+    // U lists: stable by U rank (the V lists' entries without their sign), with both
+    // directions of the cross positions
+    const int np = radix_passes(bits_u);
+    uint32_t* xkey = (m > 4096 && np >= 3 && (np & 1)) ? e[0] : e[3];
+    radix_sort_to(T.ent + m, SortBufs{e[0], e[1], e[2]}, SortBufs{e[3], e[5], T.mstart}, e[4], nullptr, true,
+                  (uint32_t)m, SortBufs{xkey, T.ent, T.cross}, reinterpret_cast<int32_t*>(T.cross), m, 0, bits_u, P.hist,
+                  P.hist_scan, P.partials, s);
+
+    const int64_t n_max = std::max(nu, nv);
+    int lw = 0;
+    while ((2 << lw) <= J.top_words) ++lw;
+    // narrower bands where a side holds few, so that the bands of the
+    // heaviest vertices spread over the chip
+    while (lw > 9 && ((int64_t)16 << lw) > n_max) --lw;
+    top_vertices(T.degr, T.cstart, nu, nv, J.s_is_u ? 1 : 0, lw, T.thr, T.kx, T.work, T.bands, T.tc, st, s);
+    top_index(T.off, T.ent, xkey, e[4], m, nu, n, T.bands, T.icnt, T.ioff, T.idx, P.partials, st, s);
+    uint32_t* mbase = e[1];  // and e[2]
+    top_work(xkey, e[4], T.ent, T.cross, T.off, T.thr, T.ioff, m, (int32_t)nu, T.mstart, mbase, T.kx, T.work, st, s);
+    top_schedule(T.work, T.kx, nu, n, (uint32_t)J.light_w, T.key, st, s);
+    radix_sort_to(T.key, SortBufs{}, SortBufs{}, nullptr, nullptr, true, 0u, SortBufs{T.vk_a, nullptr, T.order},
+                  nullptr, n, 0, 8, P.hist, P.hist_scan, P.partials, s);
+    top_counts(T.vk_a, n, T.tc, s);
+    if (ev) (void)hipEventRecord(ev[1], s);
+
+    const TopArgs a{T.ent,  T.cross, T.mstart, mbase, T.off, T.kx, T.order, T.idx, T.work, T.bands, st, T.tc, T.inv,
+                    (int32_t)nu, J.schedule == BBC_SCHED_STATIC ? 1 : 0, J.queue_chunk, J.light_chunk};
+    launch_top(J.top_words, J.top_wg, J.top_grid, J.light_grid, J.n_cu, a, s);
+    if (ev) (void)hipEventRecord(ev[2], s);
+}
+
 // Queues the whole pipeline on stream s: kernel launches only (no host
 // waits, copies or allocations), so it can be captured in a graph.
 // ev (optional) receives [after checks, after build, after count].
@@ -365,7 +490,7 @@ void enqueue(const Job& J, Plan& P, DevStatus* st, hipStream_t s, hipEvent_t* ev
     // are free until the centre sort
     uint32_t* ea = P.v1_a;
     uint32_t* pay = P.v1_b;
-    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(64), 0, s, st);
+    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, st);
     if (J.batched)
         launch_decode_batched(J.off, J.adj, J.sg, P.graphs, P.vstart, J.n_graphs, m, check_sign, st, ea, pay, s);
     else
@@ -525,6 +650,26 @@ void set_regimes(Job& J, const bbc_options& o, bool full) {
     J.queue_chunk = o.queue_chunk > 0 ? o.queue_chunk : 1;
     const int lmax = wedge_light_max(o.band_words, o.wg_size);
     J.light_w = (full || o.wave_max_work < 0) ? 0 : o.wave_max_work == 0 ? lmax : std::min(o.wave_max_work, lmax);
+}
+
+// Default shape of its band kernel: the widest bands for sides that fill 16 of
+// them, since what a hub's band costs is its middles, visited once per band;
+// smaller sides get two narrower workgroups per CU.
+constexpr int kTopWords = 32768, kTopWG = 1024, kTopSmallWords = 16384, kTopSmallWG = 512;
+
+// Top-vertex pipeline of a job whose sizes and options are set.
+void set_top(const bbc_ctx* ctx, Job& J, const bbc_options& o) {
+    if (!top_fits(J)) return;
+    J.top = true;
+    const bool fixed = o.band_words || o.wg_size;
+    const bool large = std::max(J.n_u, J.n_v) >= 16 * kTopWords;
+    J.top_words = fixed ? wedge_band(o.band_words, o.wg_size, false) : large ? kTopWords : kTopSmallWords;
+    J.top_wg = fixed ? wedge_block(o.band_words, o.wg_size, false) : large ? kTopWG : kTopSmallWG;
+    J.top_grid = ctx->n_cu * (o.wg_per_cu > 0 ? o.wg_per_cu : top_blocks_per_cu(J.top_words, J.top_wg));
+    J.grid = J.top_grid;
+    J.n_cu = ctx->n_cu;
+    J.light_grid = ctx->n_cu * top_light_blocks_per_cu();
+    J.light_w = std::min(J.light_w, kLightMaxWork);
 }
 
 bool side_is_u(int side, int32_t n_u, int32_t n_v) { return side == BBC_SIDE_U || (side == BBC_SIDE_AUTO && n_u < n_v); }
@@ -774,7 +919,7 @@ void fill_stats(bbc_ctx* ctx, const Job& J, const DevStatus& h, int block) {
     S.dense_ops = J.dense_ops;
     S.grid = J.grid;
     S.block = block;
-    S.band_words = wedge_band(J.band_words, J.wg_size, J.pv != nullptr);
+    S.band_words = J.top ? J.top_words : wedge_band(J.band_words, J.wg_size, J.pv != nullptr);
     S.tuned = J.tuned ? 1 : 0;
     S.schedule = J.schedule;
 }
@@ -789,6 +934,16 @@ bbc_status timed_stats(bbc_ctx* ctx) {
     return BBC_OK;
 }
 
+// Scratch bytes of a job.
+size_t job_bytes(const Job& J) {
+    if (J.top) {
+        TopPlan T;
+        return T.carve(nullptr, J);
+    }
+    Plan P;
+    return P.carve(nullptr, J);
+}
+
 // Runs a job whose buffers are carved from `arena` (large enough for it) on
 // stream s and waits for its status.
 bbc_status run_planned(bbc_ctx* ctx, const Job& J, char* arena, const bbc_options& opts, hipStream_t s,
@@ -796,7 +951,9 @@ bbc_status run_planned(bbc_ctx* ctx, const Job& J, char* arena, const bbc_option
                        const std::vector<int64_t>* rend, const std::vector<DevBlock>* db,
                        const std::vector<DevTile>* dt) {
     Plan P;
-    P.carve(arena, J);
+    TopPlan T;
+    if (J.top) T.carve(arena, J);
+    else P.carve(arena, J);
     if (dg && !dg->empty()) {
         HIP_OR_FAIL(hipMemcpyAsync(P.graphs, dg->data(), dg->size() * sizeof(DevGraph), hipMemcpyHostToDevice, s));
         HIP_OR_FAIL(hipMemcpyAsync(P.vstart, vstart->data(), vstart->size() * 8, hipMemcpyHostToDevice, s));
@@ -808,25 +965,32 @@ bbc_status run_planned(bbc_ctx* ctx, const Job& J, char* arena, const bbc_option
         HIP_OR_FAIL(hipMemcpyAsync(P.dtiles, dt->data(), dt->size() * sizeof(DevTile), hipMemcpyHostToDevice, s));
     const bool timing = opts.timing != 0;
     if (timing) HIP_OR_FAIL(hipEventRecord(ctx->ev[3], s));
-    enqueue(J, P, ctx->st_dev, s, timing ? ctx->ev : nullptr);
+    if (J.top) enqueue_top(J, T, ctx->st_dev, s, timing ? ctx->ev : nullptr);
+    else enqueue(J, P, ctx->st_dev, s, timing ? ctx->ev : nullptr);
     HIP_OR_FAIL(hipGetLastError());
     HIP_OR_FAIL(hipMemcpyAsync(ctx->st_host, ctx->st_dev, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
+    fold_sums(*ctx->st_host);
     const bbc_status rc = status_result(ctx, *ctx->st_host);
     if (rc != BBC_OK) return rc;
-    fill_stats(ctx, J, *ctx->st_host, wedge_block(J.band_words, J.wg_size, J.pv != nullptr));
+    fill_stats(ctx, J, *ctx->st_host, J.top ? J.top_wg : wedge_block(J.band_words, J.wg_size, J.pv != nullptr));
     return timing ? timed_stats(ctx) : BBC_OK;
 }
 
 // Runs a job on the context's arena (grown to fit) and stream and waits for
 // its status.
-bbc_status run_job(bbc_ctx* ctx, const Job& J, const bbc_options& opts, hipStream_t s,
+bbc_status run_job(bbc_ctx* ctx, Job& J, const bbc_options& opts, hipStream_t s,
                    const std::vector<DevGraph>* dg, const std::vector<int64_t>* vstart,
                    const std::vector<int64_t>* rend, const std::vector<DevBlock>* db = nullptr,
                    const std::vector<DevTile>* dt = nullptr) {
-    Plan P;
-    bbc_status rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, P.carve(nullptr, J));
+    bbc_status rc = BBC_ENOMEM;
+    if (J.top) {  // the one-sided walk needs less scratch: it takes over where this does not fit
+        rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, job_bytes(J));
+        if (rc == BBC_ENOMEM) J.top = false;
+    }
+    if (!J.top) rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, job_bytes(J));
     if (rc != BBC_OK) return rc;
+    ctx->err.clear();
     return run_planned(ctx, J, ctx->arena, opts, s, dg, vstart, rend, db, dt);
 }
 
@@ -1029,9 +1193,13 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
         rc = block_job(ctx, opts, J, db, dt);
         if (rc != BBC_OK) return rc;
     }
+    if (!full && opts.n_blocks == 0) set_top(ctx, J, opts);
     if (fixed) {
-        Plan P;
-        const size_t need = P.carve(nullptr, J);
+        size_t need = job_bytes(J);
+        if (J.top && (need > kFixedScratchBytes || (ctx->limit > 0 && need > (size_t)ctx->limit))) {
+            J.top = false;  // the one-sided walk needs less
+            need = job_bytes(J);
+        }
         if (ctx->limit > 0 && need > (size_t)ctx->limit)
             return fail(ctx, BBC_ENOMEM, "the call needs " + std::to_string(need) + " bytes of scratch, above its "
                                          "scratch_limit of " + std::to_string(ctx->limit));
@@ -1306,11 +1474,12 @@ bbc_status bbc_update_delta(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_ed
     D.carve(ctx->arena, m, q, n_v, hs, nmax);
     DevStatus* st = ctx->st_dev;
     // checks first (the builds below index with the ids), one wait
-    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(64), 0, s, st);
+    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, st);
     launch_decode_single(offsets, adj, signs, n_u, n_v, m, 1, 1, st, D.ea, D.ec, D.en, nullptr, s);
     dyn_check(upd_u, upd_v, upd_state, (int32_t)q, n_u, n_v, st, s);
     HIP_OR_FAIL(hipMemcpyAsync(ctx->st_host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
+    fold_sums(*ctx->st_host);
     rc = status_result(ctx, *ctx->st_host);
     if (rc != BBC_OK) return rc;
     const int bits_u = bits_for(n_u > 0 ? (uint64_t)(n_u - 1) : 0), bits_v = bits_for(n_v > 0 ? (uint64_t)(n_v - 1) : 0);
@@ -1347,6 +1516,7 @@ bbc_status bbc_update_delta(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_ed
               ctx->update_task_cap, st, s);
     HIP_OR_FAIL(hipMemcpyAsync(ctx->st_host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
+    fold_sums(*ctx->st_host);
     rc = status_result(ctx, *ctx->st_host);
     if (rc != BBC_OK) return rc;
     *delta = (int64_t)ctx->st_host->total;
@@ -1435,7 +1605,7 @@ bbc_status bbc_batch_plan_create(bbc_ctx* ctx, int32_t n_graphs, const bbc_graph
     if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         if (n_graphs > 0) enqueue(J, P, p->st_dev, cs, nullptr);
-        else hipLaunchKernelGGL(k_status_init, dim3(1), dim3(64), 0, cs, p->st_dev);
+        else hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, cs, p->st_dev);
         hipError_t le = hipGetLastError();
         e = hipStreamEndCapture(cs, &p->graph);
         if (e == hipSuccess) e = le;
@@ -1673,7 +1843,7 @@ bbc_status bbc_plan_blocks(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edg
     } host_free{host};
 
     // edges as (anchor, centre) with the offset and id-range checks
-    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(64), 0, s, ctx->st_dev);
+    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, ctx->st_dev);
     launch_decode_single(offsets, adj, nullptr, n_u, n_v, m, su ? 1 : 0, 0, ctx->st_dev, ea, ec, nullptr, nullptr,
                          s);
     HIP_OR_FAIL(hipMemcpyAsync(ctx->st_host, ctx->st_dev, sizeof(DevStatus), hipMemcpyDeviceToHost, s));

@@ -8,6 +8,22 @@ namespace bbc {
 
 constexpr int kWave = 64;
 
+// Sums that many workgroups add to.  Atomics on one address are served one
+// after the other (about 18 ns each: 4,096 waves adding to one counter took
+// 75 us at the end of a kernel), so every workgroup adds to one of
+// kSumSlots copies, 128 bytes apart, and the host adds the copies up
+// (fold_sums).
+constexpr int kSumSlots = 32;
+struct DevSums {
+    unsigned long long total;   // twice the balanced butterflies
+    unsigned long long wedges;  // sum over centres of C(deg, 2)
+    unsigned long long walked;  // wedges the sparse walk visits (dense-block wedges excluded)
+    unsigned long long bands;   // counter bands processed
+    unsigned long long cls[6];  // sign-pattern classes (class mode); biclique limbs and overflows
+    unsigned long long pad[6];
+};
+static_assert(sizeof(DevSums) == 128, "one cache line per copy");
+
 // Device-side status and accumulators of one bbc_count call.
 struct DevStatus {
     int32_t flags;  // kBad* bits
@@ -25,7 +41,21 @@ struct DevStatus {
     unsigned long long cls[6];  // sign-pattern classes (class mode); biclique limbs and overflows
     unsigned int queue;         // persistent work queue head
     unsigned int n_light;       // anchors of the wave regime (listed after every other anchor)
+    alignas(128) DevSums sums[kSumSlots];
 };
+
+__device__ __forceinline__ DevSums* my_sums(DevStatus* st) { return &st->sums[blockIdx.x % kSumSlots]; }
+
+// Host: the copies' sums added to the status's own fields.
+inline void fold_sums(DevStatus& h) {
+    for (const DevSums& q : h.sums) {
+        h.total += q.total;
+        h.wedges += q.wedges;
+        h.walked += q.walked;
+        h.bands += q.bands;
+        for (int k = 0; k < 6; ++k) h.cls[k] += q.cls[k];
+    }
+}
 
 enum : int32_t {
     kBadOffsets = 1,
@@ -190,7 +220,9 @@ __device__ __forceinline__ T block_sum(T x, T* tmp) {
 // Exclusive scan: out[i] = sum(in[0..i)), out[n] = total.  `partials` needs
 // scan_partials_size(n) elements of Tacc.  in and out must not alias.
 size_t scan_partials_size(int64_t n);
-void scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials, hipStream_t s);
+// `base` is added to every result.
+void scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials, hipStream_t s,
+                        uint32_t base = 0);
 
 // Stable LSD radix sort of n uint32 keys on their low `bits` bits, carrying
 // up to two uint32 payloads.  The inputs are read only; the result lands in
@@ -205,6 +237,21 @@ void radix_sort(const uint32_t* k_in, uint32_t* k_a, uint32_t* k_b, const uint32
                 uint32_t* v0_b, const uint32_t* v1_in, uint32_t* v1_a, uint32_t* v1_b, int64_t n, int bits,
                 uint32_t* hist, uint32_t* hist_scan, uint32_t* partials, hipStream_t s, const uint32_t** k_out,
                 const uint32_t** v0_out, const uint32_t** v1_out, int32_t* inv_out = nullptr);
+
+// The same sort with every destination named: stable, on bits
+// [shift0, shift0 + bits) of the keys, passes of 8 bits (radix_passes(bits)
+// of them) going through a, b, a, ... and the last one to `out`, which may
+// share memory with whichever of the inputs, a or b that pass does not read.
+// With v1_iota payload 1 is iota0 + the input index; out.v1 may be NULL when
+// inv_out is given.
+struct SortBufs {
+    uint32_t *k, *v0, *v1;
+};
+int radix_passes(int bits);
+void radix_sort_to(const uint32_t* k_in, const SortBufs& a, const SortBufs& b, const uint32_t* v0_in,
+                   const uint32_t* v1_in, bool v1_iota, uint32_t iota0, const SortBufs& out, int32_t* inv_out,
+                   int64_t n, int shift0, int bits, uint32_t* hist, uint32_t* hist_scan, uint32_t* partials,
+                   hipStream_t s);
 
 void fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 void fill_bytes(void* p, int64_t bytes, hipStream_t s);  // zero fill

@@ -20,6 +20,7 @@
 // nothing once an input error is flagged, so the whole sequence can be
 // queued (or captured in a graph) without waiting for the checks.
 #include "bbc_internal.h"
+#include "top.h"
 
 namespace bbc {
 
@@ -121,13 +122,24 @@ __device__ __forceinline__ void dec_running_max(int32_t* marks, int32_t seed, in
     __syncthreads();
 }
 
+// Rows in rank order (the top-vertex pipeline): the rank of each U id and
+// the first position of each rank's row.
+struct RowOrder {
+    const int32_t* rank;
+    const uint32_t* off;
+};
+
 // Edge e of a single graph -> anchor id ea[e] and either pay[e] = centre id
 // | negative << 31 (the count) or ec[e] and en[e] (other users), with the
-// id-range and sign checks.
+// id-range and sign checks.  TOP: rows move to their rank's place instead,
+// ea = V id and pay = U rank | negative << 31 there (nothing is written once
+// the offsets are known to be malformed).
+template <bool TOP>
 __global__ __launch_bounds__(kDecThreads) void k_decode_single(const int32_t* off, const int32_t* adj,
                                                                const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
                                                                int s_is_u, int check_sign, DevStatus* st, uint32_t* ea,
-                                                               uint32_t* ec, uint8_t* en, uint32_t* pay) {
+                                                               uint32_t* ec, uint8_t* en, uint32_t* pay, RowOrder ro) {
+    if (TOP && (*(volatile const int32_t*)&st->flags & kBadOffsets)) return;
     __shared__ int32_t rr[2];
     __shared__ int32_t rowof[kDecChunk + kDecChunk / 16];
     __shared__ int32_t wmax[kDecThreads / kWave];
@@ -151,6 +163,13 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_single(const int32_t* of
         if (v < 0 || v >= n_v) flag_bad(st, kBadRange, &st->bad_range, e);
         if (check_sign && s != 1 && s != -1) flag_bad(st, kBadSign, &st->bad_sign, e);
         const uint32_t neg = s < 0 ? 1u : 0u;
+        if constexpr (TOP) {
+            const uint32_t r = (uint32_t)ro.rank[u];
+            const uint32_t p = ro.off[r] + (uint32_t)(e - off[u]);
+            ea[p] = (uint32_t)v;
+            pay[p] = r | (neg << 31);
+            continue;
+        }
         ea[e] = (uint32_t)(s_is_u ? u : v);
         if (pay) {
             pay[e] = (uint32_t)(s_is_u ? v : u) | (neg << 31);
@@ -470,8 +489,8 @@ __global__ __launch_bounds__(256) void k_work(const uint32_t* __restrict__ apack
     }
     all = block_sum<256>(all, red);
     walked = block_sum<256>(walked, red);
-    if (threadIdx.x == 0 && all) atomicAdd(&st->wedges, all);
-    if (threadIdx.x == 0 && walked) atomicAdd(&st->walked, walked);
+    if (threadIdx.x == 0 && all) atomicAdd(&my_sums(st)->wedges, all);
+    if (threadIdx.x == 0 && walked) atomicAdd(&my_sums(st)->walked, walked);
 }
 
 // Sort key of each anchor: the bitwise complement of its clamped work, so an
@@ -588,8 +607,17 @@ void launch_decode_single(const int32_t* off, const int32_t* adj, const int8_t* 
                           uint8_t* en, uint32_t* pay, hipStream_t s) {
     hipLaunchKernelGGL(k_check_offsets, dim3(grid_for((int64_t)n_u + 1, 256)), dim3(256), 0, s, off, n_u, m, st);
     if (m > 0)
-        hipLaunchKernelGGL(k_decode_single, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)), dim3(kDecThreads), 0, s,
-                           off, adj, sg, n_u, n_v, m, s_is_u, check_sign, st, ea, ec, en, pay);
+        hipLaunchKernelGGL(k_decode_single<false>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)), dim3(kDecThreads),
+                           0, s, off, adj, sg, n_u, n_v, m, s_is_u, check_sign, st, ea, ec, en, pay,
+                           RowOrder{nullptr, nullptr});
+}
+
+void top_decode(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
+                int check_sign, const int32_t* rank, const uint32_t* roff, DevStatus* st, uint32_t* key, uint32_t* pay,
+                hipStream_t s) {
+    hipLaunchKernelGGL(k_decode_single<true>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)), dim3(kDecThreads), 0,
+                       s, off, adj, sg, n_u, n_v, m, 1, check_sign, st, key, (uint32_t*)nullptr, (uint8_t*)nullptr,
+                       pay, RowOrder{rank, roff});
 }
 
 void launch_decode_batched(const int32_t* off_cat, const int32_t* adj_cat, const int8_t* sg_cat, const DevGraph* gr,

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256, TILE == 128 ? 2 : 4) void k_dense(const DevBlo
             }
         }
     acc = wave_sum(acc);
-    if (lane == 0 && acc) atomicAdd(&st->total, acc);
+    if (lane == 0 && acc) atomicAdd(&my_sums(st)->total, acc);
 }
 
 // The 128 x 128 tile with operands loaded straight into LDS
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(kQWaves * kWave, 2) void k_dense_lds(const DevBlock
             }
         }
     acc = wave_sum(acc);
-    if (lane == 0 && acc) atomicAdd(&st->total, acc);
+    if (lane == 0 && acc) atomicAdd(&my_sums(st)->total, acc);
 }
 
 // ------------------------------------------------------------ host launchers

@@ -495,7 +495,7 @@ __global__ __launch_bounds__(WG) void k_dyn_delta(DynView d, const uint32_t* tas
         const long long sum = block_sum<WG>(acc, sh.tmp);
         if (threadIdx.x == 0 && sum) {
             if (per_update) atomicAdd((unsigned long long*)&per_update[i], (unsigned long long)sum);
-            atomicAdd(&st->total, (unsigned long long)sum);
+            atomicAdd(&my_sums(st)->total, (unsigned long long)sum);
         }
     }
 }

@@ -61,10 +61,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* in
 }
 
 // exclusive scan of nb partials by one workgroup, in place
-__global__ __launch_bounds__(1024) void k_scan_partials(uint32_t* partial, int64_t nb) {
+__global__ __launch_bounds__(1024) void k_scan_partials(uint32_t* partial, int64_t nb, uint32_t base) {
     __shared__ uint32_t tmp[1024 / kWave + 1];
     __shared__ uint32_t carry;
-    if (threadIdx.x == 0) carry = 0;
+    if (threadIdx.x == 0) carry = base;
     __syncthreads();
     for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
         int64_t i = b0 + threadIdx.x;
@@ -81,9 +81,9 @@ __global__ __launch_bounds__(1024) void k_scan_partials(uint32_t* partial, int64
 
 // Each thread owns kScanItems consecutive inputs, staged through LDS so the
 // global reads and writes stay coalesced.  partial == NULL: a single tile
-// (no partial sums to add).
+// (no partial sums to add, only the base).
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t* in, uint32_t* out, int64_t n,
-                                                             const uint32_t* partial) {
+                                                             const uint32_t* partial, uint32_t base0) {
     __shared__ uint32_t stage[kScanTile];
     __shared__ uint32_t tmp[kScanThreads / kWave + 1];
     int64_t base = (int64_t)blockIdx.x * kScanTile;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t* in,
         s += v[k];
     }
     uint32_t tot;
-    uint32_t ex = block_exclusive_scan<kScanThreads>(s, tmp, &tot) + (partial ? partial[blockIdx.x] : 0u);
+    uint32_t ex = block_exclusive_scan<kScanThreads>(s, tmp, &tot) + (partial ? partial[blockIdx.x] : base0);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         stage[threadIdx.x * kScanItems + k] = ex;
@@ -116,20 +116,21 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t* in,
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) out[n] = ex;
 }
 
-void scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials, hipStream_t s) {
+void scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials, hipStream_t s,
+                        uint32_t base) {
     if (n <= 0) {
-        fill_u32(out, 0u, 1, s);
+        fill_u32(out, base, 1, s);
         return;
     }
     int64_t nb = (n + kScanTile - 1) / kScanTile;
     if (nb == 1) {  // one tile: one launch
-        hipLaunchKernelGGL(k_scan_apply, dim3(1), dim3(kScanThreads), 0, s, in, out, n, (const uint32_t*)nullptr);
+        hipLaunchKernelGGL(k_scan_apply, dim3(1), dim3(kScanThreads), 0, s, in, out, n, (const uint32_t*)nullptr, base);
         return;
     }
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, partials);
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials, nb);
+    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials, nb, base);
     hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, out, n,
-                       (const uint32_t*)partials);
+                       (const uint32_t*)partials, base);
 }
 
 // ------------------------------------------------------------- radix sort
@@ -140,6 +141,12 @@ constexpr int kRsTile = kRsThreads * kRsRounds;
 constexpr int kRsWaves = kRsThreads / kWave;
 
 size_t radix_hist_size(int64_t n) { return (size_t)256 * (size_t)((n + kRsTile - 1) / kRsTile) + 1; }
+
+int radix_passes(int bits) { return bits < 1 ? 1 : (bits + 7) / 8; }
+
+// Mask of a pass's digit when `left` key bits remain (key bits above the
+// sorted ones may hold anything).
+__host__ __device__ __forceinline__ uint32_t radix_mask(int left) { return left >= 8 ? 255u : (1u << left) - 1u; }
 
 // Tile of workgroup b.  Workgroups are dealt round robin over the eight
 // XCDs, so XCD x = b % 8 is given a contiguous range of tiles: consecutive
@@ -167,8 +174,8 @@ __device__ __forceinline__ unsigned long long digit_peers(uint32_t d, bool valid
 // When every lane of a wave holds the same digit (the high digits of
 // narrow or grouped keys) one lane adds them all, instead of 64 atomics on
 // one LDS word.
-__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, int64_t n, int shift, uint32_t* hist,
-                                                        int64_t nblk) {
+__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, int64_t n, int shift, uint32_t dmask,
+                                                        uint32_t* hist, int64_t nblk) {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, in
     for (int r = 0; r < kRsRounds; ++r) {
         const int64_t i = base + (int64_t)r * kRsThreads + threadIdx.x;
         const bool valid = i < n;
-        const uint32_t d = valid ? (keys[i] >> shift) & 255u : 0u;
+        const uint32_t d = valid ? (keys[i] >> shift) & dmask : 0u;
         const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
         if (__all(d == d0 || !valid)) {
             const unsigned long long vm = __ballot(valid);
@@ -205,13 +212,14 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, in
 // at its global offset (the digit of each place is kept in LDS for the
 // payloads).  Keys and places stay in registers between the phases; each
 // payload is read when its turn comes.  One buffer and few registers let
-// six tiles run per CU (26 KB of LDS each).  With inv_out the
-// second payload is not moved: inv_out[v1] receives the item's new position
-// instead (the inverse of the permutation that payload tracks).
+// six tiles run per CU (26 KB of LDS each).  With inv_out,
+// inv_out[v1] receives the item's new position (the inverse of the
+// permutation that payload tracks); v1_out may then be NULL.
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys, uint32_t* keys_out,
                                                            const uint32_t* v0, uint32_t* v0_out,
                                                            const uint32_t* v1, uint32_t* v1_out, int v1_iota,
-                                                           int32_t* inv_out, int64_t n, int shift,
+                                                           uint32_t iota0, int32_t* inv_out, int64_t n, int shift,
+                                                           uint32_t dmask,
                                                            const uint32_t* hist, const uint32_t* hist_scan,
                                                            int64_t nblk) {
     __shared__ uint32_t s_buf[kRsTile];
@@ -245,7 +253,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
 #pragma unroll
     for (int r = 0; r < kRsRounds; ++r) {
         const bool valid = base + (uint32_t)(r * kWave + lane) < n32;
-        const uint32_t d = (key[r] >> shift) & 255u;
+        const uint32_t d = (key[r] >> shift) & dmask;
         const unsigned long long peers = digit_peers(d, valid);
         const uint32_t rk = (uint32_t)__popcll(peers & below);
         const uint32_t run = wcnt[w][d];
@@ -266,7 +274,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
     // places in the sorted tile (invalid items get none)
 #pragma unroll
     for (int r = 0; r < kRsRounds; ++r) {
-        const uint32_t d = (key[r] >> shift) & 255u;
+        const uint32_t d = (key[r] >> shift) & dmask;
         place[r] = base + (uint32_t)(r * kWave + lane) < n32 ? wcnt[w][d] + place[r] : 0xffffffffu;
     }
     const uint32_t tbase = (uint32_t)tile * kRsTile;
@@ -276,7 +284,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
     for (int r = 0; r < kRsRounds; ++r) {
         if (place[r] != 0xffffffffu) {
             s_buf[place[r]] = key[r];
-            s_dig[place[r]] = (uint8_t)((key[r] >> shift) & 255u);
+            s_dig[place[r]] = (uint8_t)((key[r] >> shift) & dmask);
         }
     }
     __syncthreads();
@@ -303,7 +311,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
 #pragma unroll
         for (int r = 0; r < kRsRounds; ++r) {
             const uint32_t i = base + (uint32_t)(r * kWave + lane);
-            b[r] = place[r] != 0xffffffffu ? (v1_iota ? i : v1[i]) : 0u;
+            b[r] = place[r] != 0xffffffffu ? (v1_iota ? iota0 + i : v1[i]) : 0u;
         }
         __syncthreads();
 #pragma unroll
@@ -314,7 +322,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
             const uint32_t d = s_dig[p];
             const uint32_t g = gstart[d] + (p - lstart[d]);
             if (inv_out) inv_out[s_buf[p]] = (int32_t)g;
-            else v1_out[g] = s_buf[p];
+            if (v1_out) v1_out[g] = s_buf[p];
         }
     }
 }
@@ -326,8 +334,8 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
 // where the launches of the multi-tile passes would dominate.
 __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, uint32_t* keys_out,
                                                           const uint32_t* v0, uint32_t* v0_out, const uint32_t* v1,
-                                                          uint32_t* v1_out, int v1_iota, int32_t* inv_out, int n,
-                                                          int bits) {
+                                                          uint32_t* v1_out, int v1_iota, uint32_t iota0,
+                                                          int32_t* inv_out, int n, int shift0, int bits) {
     __shared__ uint32_t s_key[kRsTile];
     __shared__ uint32_t s_v0[kRsTile];
     __shared__ uint32_t s_v1[kRsTile];
@@ -338,11 +346,12 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
     for (int i = t; i < n; i += kRsThreads) {
         s_key[i] = keys[i];
         if (with_v0) s_v0[i] = v0[i];
-        if (with_v1) s_v1[i] = v1_iota ? (uint32_t)i : v1[i];
+        if (with_v1) s_v1[i] = v1_iota ? iota0 + (uint32_t)i : v1[i];
     }
     const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
     const int base = w * (kRsRounds * kWave);
-    for (int shift = 0; shift < bits; shift += 8) {
+    for (int shift = shift0; shift < shift0 + bits; shift += 8) {
+        const uint32_t dmask = radix_mask(shift0 + bits - shift);
         __syncthreads();  // the previous pass's items are in place
         uint32_t key[kRsRounds], a[kRsRounds], b[kRsRounds], place[kRsRounds];
 #pragma unroll
@@ -359,7 +368,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
 #pragma unroll
         for (int r = 0; r < kRsRounds; ++r) {
             const bool valid = base + r * kWave + lane < n;
-            const uint32_t d = (key[r] >> shift) & 255u;
+            const uint32_t d = (key[r] >> shift) & dmask;
             const unsigned long long peers = digit_peers(d, valid);
             const uint32_t rk = (uint32_t)__popcll(peers & below);
             const uint32_t run = wcnt[w][d];
@@ -382,7 +391,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
 #pragma unroll
         for (int r = 0; r < kRsRounds; ++r) {
             if (base + r * kWave + lane < n) {
-                const uint32_t pos = wcnt[w][(key[r] >> shift) & 255u] + place[r];
+                const uint32_t pos = wcnt[w][(key[r] >> shift) & dmask] + place[r];
                 s_key[pos] = key[r];
                 if (with_v0) s_v0[pos] = a[r];
                 if (with_v1) s_v1[pos] = b[r];
@@ -394,7 +403,41 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
         keys_out[i] = s_key[i];
         if (with_v0) v0_out[i] = s_v0[i];
         if (inv_out) inv_out[s_v1[i]] = i;
-        else if (with_v1) v1_out[i] = s_v1[i];
+        if (v1_out) v1_out[i] = s_v1[i];
+    }
+}
+
+void radix_sort_to(const uint32_t* k_in, const SortBufs& a, const SortBufs& b, const uint32_t* v0_in,
+                   const uint32_t* v1_in, bool v1_iota, uint32_t iota0, const SortBufs& out, int32_t* inv_out,
+                   int64_t n, int shift0, int bits, uint32_t* hist, uint32_t* hist_scan, uint32_t* partials,
+                   hipStream_t s) {
+    if (n <= 0) return;
+    if (bits < 1) bits = 1;
+    const bool with_v1 = v1_iota || v1_in != nullptr;
+    const int64_t nblk = (n + kRsTile - 1) / kRsTile;
+    if (nblk == 1) {  // one tile: every pass in one launch
+        hipLaunchKernelGGL(k_rs_single, dim3(1), dim3(kRsThreads), 0, s, k_in, out.k, v0_in, v0_in ? out.v0 : nullptr,
+                           v1_in, with_v1 ? out.v1 : nullptr, v1_iota ? 1 : 0, iota0, inv_out, (int)n, shift0, bits);
+        return;
+    }
+    const int n_pass = radix_passes(bits);
+    const uint32_t *ks = k_in, *v0s = v0_in, *v1s = v1_in;
+    int iota = v1_iota ? 1 : 0;
+    for (int pass = 0; pass < n_pass; ++pass) {
+        const bool last = pass == n_pass - 1;
+        const SortBufs& d = last ? out : (pass & 1) ? b : a;
+        const int shift = shift0 + 8 * pass;
+        const uint32_t dmask = radix_mask(bits - 8 * pass);
+        hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nblk), dim3(kRsThreads), 0, s, ks, n, shift, dmask, hist, nblk);
+        scan_exclusive_u32(hist, hist_scan, 256 * nblk, partials, s);
+        hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nblk), dim3(kRsThreads), 0, s, ks, d.k, v0s,
+                           v0_in ? d.v0 : nullptr, v1s, with_v1 ? d.v1 : nullptr, iota, iota0,
+                           last ? inv_out : nullptr, n, shift, dmask, (const uint32_t*)hist, (const uint32_t*)hist_scan,
+                           nblk);
+        ks = d.k;
+        v0s = v0_in ? d.v0 : nullptr;
+        v1s = d.v1;
+        iota = 0;
     }
 }
 
@@ -402,40 +445,19 @@ void radix_sort(const uint32_t* k_in, uint32_t* k_a, uint32_t* k_b, const uint32
                 uint32_t* v0_b, const uint32_t* v1_in, uint32_t* v1_a, uint32_t* v1_b, int64_t n, int bits,
                 uint32_t* hist, uint32_t* hist_scan, uint32_t* partials, hipStream_t s, const uint32_t** k_out,
                 const uint32_t** v0_out, const uint32_t** v1_out, int32_t* inv_out) {
-    const uint32_t *ks = k_in, *v0s = v0_in, *v1s = v1_in;
-    int v1_iota = (v1_a != nullptr && v1_in == nullptr) ? 1 : 0;
-    int64_t nblk = (n + kRsTile - 1) / kRsTile;
-    if (bits < 1) bits = 1;
-    if (n > 0 && nblk == 1) {  // one tile: every pass in one launch
-        uint32_t* v0d = v0_in ? v0_a : nullptr;
-        uint32_t* v1d = (v1_a && !inv_out) ? v1_a : nullptr;
-        hipLaunchKernelGGL(k_rs_single, dim3(1), dim3(kRsThreads), 0, s, k_in, k_a, v0_in, v0d, v1_in, v1d, v1_iota,
-                           inv_out, (int)n, bits);
-        *k_out = k_a;
-        if (v0_out) *v0_out = v0d;
-        if (v1_out) *v1_out = v1d;
-        return;
-    }
-    const int n_pass = (bits + 7) / 8;
-    int pass = 0;
-    for (int shift = 0; shift < bits && n > 0; shift += 8, ++pass) {
-        uint32_t* kd = (pass & 1) ? k_b : k_a;
-        uint32_t* v0d = v0_in ? ((pass & 1) ? v0_b : v0_a) : nullptr;
-        int32_t* inv = (inv_out && pass == n_pass - 1) ? inv_out : nullptr;
-        uint32_t* v1d = (v1_a && !inv) ? ((pass & 1) ? v1_b : v1_a) : nullptr;
-        hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nblk), dim3(kRsThreads), 0, s, ks, n, shift, hist, nblk);
-        scan_exclusive_u32(hist, hist_scan, 256 * nblk, partials, s);
-        hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nblk), dim3(kRsThreads), 0, s, ks, kd, v0s, v0d, v1s,
-                           v1d, v1_iota, inv, n, shift, (const uint32_t*)hist,
-                           (const uint32_t*)hist_scan, nblk);
-        ks = kd;
-        v0s = v0d;
-        v1s = v1d;
-        v1_iota = 0;
-    }
-    *k_out = ks;
-    if (v0_out) *v0_out = v0s;
-    if (v1_out) *v1_out = v1s;
+    // payload 1 is the input index when only its buffers are given; the
+    // result lies in the buffer pair the last pass wrote (the inputs when
+    // there is nothing to sort)
+    const bool iota = v1_a != nullptr && v1_in == nullptr;
+    const bool odd = n <= kRsTile || (radix_passes(bits) & 1);
+    const SortBufs a{k_a, v0_a, v1_a}, b{k_b, v0_b, v1_b};
+    SortBufs out = odd ? a : b;
+    if (inv_out) out.v1 = nullptr;
+    if (n > 0)
+        radix_sort_to(k_in, a, b, v0_in, v1_in, iota, 0u, out, inv_out, n, 0, bits, hist, hist_scan, partials, s);
+    *k_out = n > 0 ? out.k : k_in;
+    if (v0_out) *v0_out = n > 0 ? (v0_in ? out.v0 : nullptr) : v0_in;
+    if (v1_out) *v1_out = n > 0 ? out.v1 : v1_in;
 }
 
 }  // namespace bbc

@@ -1,0 +1,133 @@
+"""Totals counted at each butterfly's highest vertex: the sizes where the
+kernels' regimes meet (waves, the two hashed tables, counter bands), counters
+that overflow a hashed slot, every counter width of the bands, band widths
+below and above a side, unindexed lists, the largest side ratio, and batches,
+all against the oracle (whole numbers: equality)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_17707_amd import bbc, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import __graft_entry__
+
+    __graft_entry__._ensure_built()
+    c = bbc.Context(0)
+    yield c
+    c.close()
+
+
+def gpu(ctx, g, **kw):
+    off, adj, sg = bbc.graph_tensors(g, "cuda:0")
+    return ctx.count(off, adj, sg, g.n_v, opts=bbc.options(**kw))
+
+
+def star_pairs(n_mid, n_end, seed, extra=0):
+    """One U hub over n_mid V vertices, each of which also holds n_end U
+    vertices: the hub walks about n_mid * n_end wedges; `extra` pendant edges
+    raise the hub's degree."""
+    rng = np.random.default_rng(seed)
+    u, v = [np.zeros(n_mid + extra, np.int64)], [np.arange(n_mid + extra)]
+    n_u = max(2 * n_end, 4)
+    for m in range(n_mid):
+        w = 1 + rng.choice(n_u, n_end, replace=False)
+        u.append(w)
+        v.append(np.full(n_end, m))
+    u, v = np.concatenate(u), np.concatenate(v)
+    return synth.from_edges(n_u + 1, n_mid + extra, u, v, np.where(rng.random(u.size) < 0.4, -1, 1))
+
+
+# (middles, endpoints each): work around the bounds of the regimes (1,024 for a
+# wave with at most 63 middles, 4,096 and 16,384 for the tables)
+@pytest.mark.parametrize("n_mid,n_end", [(2, 1), (63, 16), (64, 16), (33, 31), (64, 63), (65, 64), (127, 128),
+                                         (129, 128), (600, 40)])
+@pytest.mark.parametrize("light", [0, -1])
+def test_regime_edges(ctx, n_mid, n_end, light):
+    g = star_pairs(n_mid, n_end, n_mid * 1000 + n_end)
+    assert gpu(ctx, g, wave_max_work=light) == oracle.count(g)
+
+
+@pytest.mark.parametrize("mids,dense", [(70, 60), (130, 30), (300, 12)])
+def test_hashed_counter_overflow(ctx, mids, dense):
+    """More than 63 common middles for one pair: the hashed count gives way to
+    the bands."""
+    rng = np.random.default_rng(mids)
+    u, v = np.meshgrid(np.arange(dense), np.arange(mids), indexing="ij")
+    u, v = u.ravel(), v.ravel()
+    g = synth.from_edges(dense + 5, mids + 3, u, v, np.where(rng.random(u.size) < 0.1, -1, 1))
+    for light in (0, -1):
+        assert gpu(ctx, g, wave_max_work=light) == oracle.count(g)
+
+
+@pytest.mark.parametrize("bw,wg", [(0, 0)] + list(bbc.WEDGE_SHAPES))
+def test_band_widths(ctx, bw, wg):
+    """Degrees in every counter width (4 to 32 bits) over sides wider than a
+    band, at every shape."""
+    rng = np.random.default_rng(5)
+    parts_u, parts_v = [], []
+    n_u, n_v = 90_000, 70_000
+    for i, d in enumerate([66_000, 65_600, 30_000, 900, 300, 255, 200, 16, 15]):
+        parts_u.append(np.full(d, i))
+        parts_v.append(rng.choice(n_v, d, replace=False))
+        parts_u.append(rng.choice(n_u - 20, min(d, 60_000), replace=False) + 20)
+        parts_v.append(np.full(min(d, 60_000), n_v - 1 - i))
+    u, v = np.concatenate(parts_u), np.concatenate(parts_v)
+    ru, rv = rng.integers(20, n_u, 300_000), rng.integers(0, n_v - 10, 300_000)
+    key = np.unique(np.concatenate([u * n_v + v, ru * n_v + rv]))
+    s = np.where(rng.random(key.size) < 0.3, -1, 1)
+    g = synth.from_edges(n_u, n_v, key // n_v, key % n_v, s)
+    want = _WANT.setdefault("widths", None) or oracle.count(g)
+    _WANT["widths"] = want
+    assert gpu(ctx, g, band_words=bw, wg_size=wg) == want
+
+
+_WANT = {}
+
+
+@pytest.mark.parametrize("n_u,n_v", [(80_000, 10_000), (80_001, 10_000), (10_000, 80_000), (10_000, 80_001)])
+def test_side_ratio_edge(ctx, n_u, n_v):
+    g = synth.chung_lu_graph(n_u, n_v, 250_000, 2.1, 2.1, min(3000, n_v // 4), min(3000, n_u // 4), n_u + n_v)
+    want = oracle.count(g)
+    for side in ("auto", "u", "v", "min_wedges"):
+        assert gpu(ctx, g, side=side) == want
+
+
+@pytest.mark.parametrize("schedule", ["dynamic", "static"])
+@pytest.mark.parametrize("chunk", [1, 7])
+def test_batch_with_heavy_graphs(ctx, schedule, chunk):
+    """Per-graph totals where graphs span every regime, empty ones between."""
+    graphs = [synth.chung_lu_graph(3000, 2500, 60_000, 2.0, 2.0, 800, 900, 1),
+              synth.from_edges(3, 4, [], [], []),
+              synth.complete_graph(90, 80),
+              synth.uniform_graph(50, 40, 300, 0.3, 2),
+              synth.from_edges(0, 0, [], [], []),
+              synth.chung_lu_graph(40_000, 30_000, 300_000, 2.1, 2.1, 3000, 3000, 3)]
+    want = [oracle.count(g) for g in graphs]
+    batch = bbc.Batch(graphs, "cuda:0")
+    o = bbc.options(schedule=schedule, queue_chunk=chunk)
+    assert ctx.count_batched(batch, opts=o).cpu().tolist() == want
+    plan = ctx.plan(batch, opts=o)
+    for _ in range(3):
+        plan.launch()
+        assert plan.wait().cpu().tolist() == want
+        assert gpu(ctx, graphs[0]) == want[0]
+    plan.close()
+
+
+def test_limits_fall_back(ctx):
+    """A scratch limit that only the one-sided walk meets keeps its result."""
+    g = synth.chung_lu_graph(20_000, 9_000, 150_000, 2.1, 2.1, 800, 800, 3, p_neg=0.3)
+    want = oracle.count(g)
+    ok = 0
+    for mib in (5, 6, 7, 8, 9, 10, 12, 14, 16, 20):
+        try:
+            assert gpu(ctx, g, scratch_limit=mib << 20) == want
+            ok += 1
+        except bbc.BbcError as e:
+            assert e.status == bbc.ENOMEM and ok == 0
+    assert ok >= 3
