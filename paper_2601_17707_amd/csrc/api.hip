@@ -64,6 +64,11 @@ void launch_block_pack(const uint32_t* ablk1, int32_t r_first, int32_t n_s, cons
                        const int32_t* cidx, int8_t* mats, const DevStatus* st, hipStream_t s);
 void launch_dense(const DevBlock* blocks, const DevTile* tiles, int32_t n_tiles, const int8_t* mats, uint32_t* tabs,
                   DevStatus* st, int tile, hipStream_t s);
+void launch_matrix_build(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
+                         int s_is_u, int check_sign, int8_t* mat, int64_t bytes, int64_t kpad, DevStatus* st,
+                         hipStream_t s);
+void launch_matrix_pairs(const int8_t* mat, int32_t n_r, int32_t rpad, int32_t kpad, int tile, DevStatus* st,
+                         hipStream_t s);
 void launch_bidx(const uint32_t* ckey, const uint32_t* coff, const uint32_t* packed, int64_t m, int64_t n_c, int gs,
                  uint32_t* nb, uint32_t* ioff, uint32_t* idx, int2* meta, uint32_t* partials, const DevStatus* st,
                  hipStream_t s);
@@ -271,6 +276,9 @@ struct Job {
     // top-vertex pipeline (totals without dense blocks; see top.h)
     bool top = false;
     int top_words = 0, top_wg = 0, top_grid = 0, light_grid = 0, n_cu = 0;
+    // sign matrix of the whole graph and its products (small sides)
+    bool mat = false;
+    int32_t mat_tile = 0, mat_rpad = 0, mat_kpad = 0;
 };
 
 // Whether the job takes the top-vertex pipeline: positions of both sides'
@@ -284,6 +292,8 @@ bool top_fits(const Job& J) {
     return J.m > 0 && J.m <= (1ll << 29) && J.n_u >= 1 && J.n_v >= 1 && J.n_u <= kTopRatio * J.n_v &&
            J.n_v <= kTopRatio * J.n_u;
 }
+
+int64_t matrix_bytes(const Job& J) { return (int64_t)J.mat_rpad * J.mat_kpad; }
 
 // All device buffers of one pass, carved from an arena in a fixed order.
 struct Plan {
@@ -479,6 +489,19 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
     if (ev) (void)hipEventRecord(ev[2], s);
 }
 
+// Queues the matrix count on stream s: the sign matrix (anchors x centres, in
+// id order) and the pair terms of its two products.
+void enqueue_matrix(const Job& J, int8_t* mat, DevStatus* st, hipStream_t s, hipEvent_t* ev) {
+    const int check_sign = (J.checks & BBC_CHECK_SIGNS) ? 1 : 0;
+    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, st);
+    if (ev) (void)hipEventRecord(ev[0], s);
+    launch_matrix_build(J.off, J.adj, J.sg, J.n_u, J.n_v, J.m, J.s_is_u ? 1 : 0, check_sign, mat, matrix_bytes(J),
+                        J.mat_kpad, st, s);
+    if (ev) (void)hipEventRecord(ev[1], s);
+    launch_matrix_pairs(mat, (int32_t)J.n_s, J.mat_rpad, J.mat_kpad, J.mat_tile, st, s);
+    if (ev) (void)hipEventRecord(ev[2], s);
+}
+
 // Queues the whole pipeline on stream s: kernel launches only (no host
 // waits, copies or allocations), so it can be captured in a graph.
 // ev (optional) receives [after checks, after build, after count].
@@ -670,6 +693,37 @@ void set_top(const bbc_ctx* ctx, Job& J, const bbc_options& o) {
     J.n_cu = ctx->n_cu;
     J.light_grid = ctx->n_cu * top_light_blocks_per_cu();
     J.light_w = std::min(J.light_w, kLightMaxWork);
+}
+
+// Matrix count of a job whose sizes are set: the signed adjacency matrix S of
+// the whole graph as bytes, and the pair terms of S S^T and |S| |S|^T on the
+// matrix cores: no ranks, lists or schedule, and five launches instead of
+// about forty.  Its time in us is close to the sum of 40 for the launches and
+// the status copy, the clearing (3 MB per us), the products (1.2 to 2.3 Gops
+// per us with 64- and 128-row tiles) and an atomic per edge (25K per us); the
+// walks take at least 120, growing to 300 at 30K edges, and 0.1 per 1000
+// edges, whatever the degrees (more the more wedges they have).  Measured,
+// matrix against walk: 32 and 156 us (30 x 20, 100 edges), 65 and 246 (2000 x
+// 1000, 20K), 178 and 337 (5000 x 5000, 75K), 289 and 341 (10000 x 5000,
+// 150K), 913 and 348 (10000 x 10000, 200K), 151 and 1491 (3000 x 3000, 2M),
+// 322 and 354 (40000 x 2000, 400K).  The line lies 15% below the walk's.  The
+// output tiles have 64 rows where the larger ones would number less than one
+// per CU (103 and 114 us at 2500 rows, 101 and 92 us at 3000).
+constexpr int64_t kMatMaxBytes = 64ll << 20;  // a graph of few edges should not grow the arena beyond that
+void set_matrix(Job& J, int n_cu) {
+    // one pair's counts fit 16 bits; a repeated edge is not counted twice here
+    if (J.m <= 0 || J.n_s < 2 || J.n_c < 1 || J.n_c > 65535 || !(J.checks & BBC_CHECK_DUPLICATES)) return;
+    const int64_t t = (J.n_s + 127) / 128;
+    const int32_t tile = t * (t + 1) / 2 < n_cu ? 64 : 128;
+    const int64_t rpad = (J.n_s + tile - 1) / tile * tile, kpad = (J.n_c + 63) / 64 * 64;
+    const double bytes = (double)rpad * kpad, ops = 2.0 * rpad * bytes, m = (double)J.m;
+    const double matrix = 40 + bytes / 3e6 + ops / (tile == 64 ? 1.2e9 : 2.2e9) + m / 25e3;
+    const double walk = 0.85 * (120 + 180 * std::min(1.0, m / 30e3) + m / 10e3);
+    if (bytes > kMatMaxBytes || matrix > walk) return;
+    J.mat = true;
+    J.mat_tile = tile;
+    J.mat_rpad = (int32_t)rpad;
+    J.mat_kpad = (int32_t)kpad;
 }
 
 bool side_is_u(int side, int32_t n_u, int32_t n_v) { return side == BBC_SIDE_U || (side == BBC_SIDE_AUTO && n_u < n_v); }
@@ -936,6 +990,7 @@ bbc_status timed_stats(bbc_ctx* ctx) {
 
 // Scratch bytes of a job.
 size_t job_bytes(const Job& J) {
+    if (J.mat) return (size_t)matrix_bytes(J);
     if (J.top) {
         TopPlan T;
         return T.carve(nullptr, J);
@@ -953,7 +1008,7 @@ bbc_status run_planned(bbc_ctx* ctx, const Job& J, char* arena, const bbc_option
     Plan P;
     TopPlan T;
     if (J.top) T.carve(arena, J);
-    else P.carve(arena, J);
+    else if (!J.mat) P.carve(arena, J);
     if (dg && !dg->empty()) {
         HIP_OR_FAIL(hipMemcpyAsync(P.graphs, dg->data(), dg->size() * sizeof(DevGraph), hipMemcpyHostToDevice, s));
         HIP_OR_FAIL(hipMemcpyAsync(P.vstart, vstart->data(), vstart->size() * 8, hipMemcpyHostToDevice, s));
@@ -965,7 +1020,8 @@ bbc_status run_planned(bbc_ctx* ctx, const Job& J, char* arena, const bbc_option
         HIP_OR_FAIL(hipMemcpyAsync(P.dtiles, dt->data(), dt->size() * sizeof(DevTile), hipMemcpyHostToDevice, s));
     const bool timing = opts.timing != 0;
     if (timing) HIP_OR_FAIL(hipEventRecord(ctx->ev[3], s));
-    if (J.top) enqueue_top(J, T, ctx->st_dev, s, timing ? ctx->ev : nullptr);
+    if (J.mat) enqueue_matrix(J, reinterpret_cast<int8_t*>(arena), ctx->st_dev, s, timing ? ctx->ev : nullptr);
+    else if (J.top) enqueue_top(J, T, ctx->st_dev, s, timing ? ctx->ev : nullptr);
     else enqueue(J, P, ctx->st_dev, s, timing ? ctx->ev : nullptr);
     HIP_OR_FAIL(hipGetLastError());
     HIP_OR_FAIL(hipMemcpyAsync(ctx->st_host, ctx->st_dev, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
@@ -983,15 +1039,25 @@ bbc_status run_job(bbc_ctx* ctx, Job& J, const bbc_options& opts, hipStream_t s,
                    const std::vector<DevGraph>* dg, const std::vector<int64_t>* vstart,
                    const std::vector<int64_t>* rend, const std::vector<DevBlock>* db = nullptr,
                    const std::vector<DevTile>* dt = nullptr) {
-    bbc_status rc = BBC_ENOMEM;
-    if (J.top) {  // the one-sided walk needs less scratch: it takes over where this does not fit
-        rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, job_bytes(J));
-        if (rc == BBC_ENOMEM) J.top = false;
+    bbc_status rc = BBC_OK;
+    if (J.top || J.mat) {
+        // the one-sided walk decides what a scratch limit refuses; it takes
+        // over where the others do not fit
+        Job one = J;
+        one.top = one.mat = false;
+        const size_t need = job_bytes(J);
+        const bool refused = ctx->limit > 0 && job_bytes(one) > (size_t)ctx->limit;
+        if (refused || grow(ctx, &ctx->arena, &ctx->arena_bytes, need) != BBC_OK) J.top = J.mat = false;
     }
-    if (!J.top) rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, job_bytes(J));
+    if (!J.top && !J.mat) rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, job_bytes(J));
     if (rc != BBC_OK) return rc;
     ctx->err.clear();
-    return run_planned(ctx, J, ctx->arena, opts, s, dg, vstart, rend, db, dt);
+    rc = run_planned(ctx, J, ctx->arena, opts, s, dg, vstart, rend, db, dt);
+    if (rc == BBC_EDUP && (J.top || J.mat)) {  // reported by its place in the one-sided walk's lists
+        J.top = J.mat = false;
+        return run_job(ctx, J, opts, s, dg, vstart, rend, db, dt);
+    }
+    return rc;
 }
 
 // Autotuning of the wedge kernel, shared by the single-graph and the
@@ -1179,6 +1245,8 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
     J.n_c = J.s_is_u ? n_v : n_u;
     J.checks = opts.checks;
     const bool full = per_vertex != nullptr;
+    const bool open = !(opts.band_words || opts.wg_size || opts.wg_per_cu || opts.schedule || opts.queue_chunk ||
+                        opts.wave_max_work);  // no knob of the walk is set
     J.tuned = apply_tuning(ctx, opts, J.n_s, n_edges, full);
     J.band_words = opts.band_words;
     J.schedule = opts.schedule;
@@ -1193,13 +1261,16 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
         rc = block_job(ctx, opts, J, db, dt);
         if (rc != BBC_OK) return rc;
     }
-    if (!full && opts.n_blocks == 0) set_top(ctx, J, opts);
+    if (!full && opts.n_blocks == 0) {
+        if (open) set_matrix(J, ctx->n_cu);
+        if (!J.mat) set_top(ctx, J, opts);
+    }
     if (fixed) {
-        size_t need = job_bytes(J);
-        if (J.top && (need > kFixedScratchBytes || (ctx->limit > 0 && need > (size_t)ctx->limit))) {
-            J.top = false;  // the one-sided walk needs less
-            need = job_bytes(J);
-        }
+        const auto fits = [&](size_t b) { return b <= kFixedScratchBytes && (ctx->limit <= 0 || b <= (size_t)ctx->limit); };
+        Job one = J;
+        one.top = one.mat = false;
+        const size_t need = job_bytes(one);  // what decides a refusal
+        if (!fits(need) || !fits(job_bytes(J))) J = one;
         if (ctx->limit > 0 && need > (size_t)ctx->limit)
             return fail(ctx, BBC_ENOMEM, "the call needs " + std::to_string(need) + " bytes of scratch, above its "
                                          "scratch_limit of " + std::to_string(ctx->limit));
@@ -1208,6 +1279,9 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
                                               " bytes of scratch, the fixed scratch holds " +
                                               std::to_string(kFixedScratchBytes));
         rc = run_planned(ctx, J, ctx->fixed, opts, (hipStream_t)stream, nullptr, nullptr, nullptr, nullptr, nullptr);
+        if (rc == BBC_EDUP && (J.top || J.mat))
+            rc = run_planned(ctx, one, ctx->fixed, opts, (hipStream_t)stream, nullptr, nullptr, nullptr, nullptr,
+                             nullptr);
     } else {
         rc = run_job(ctx, J, opts, (hipStream_t)stream, nullptr, nullptr, nullptr, &db, &dt);
     }

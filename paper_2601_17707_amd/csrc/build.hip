@@ -38,12 +38,14 @@ __device__ __forceinline__ bool input_bad(const DevStatus* st) { return *(volati
 // ------------------------------------------------------------------ checks
 
 // offsets[0] == 0, offsets[n_u] == m, non-decreasing
+__device__ __forceinline__ void check_offset(const int32_t* off, int32_t n_u, int64_t m, int64_t i, DevStatus* st) {
+    int32_t o = off[i];
+    bool bad = (i == 0 && o != 0) || (i == n_u && (int64_t)o != m) || (i < n_u && off[i + 1] < o);
+    if (bad) flag_bad(st, kBadOffsets, &st->bad_offset, i);
+}
+
 __global__ void k_check_offsets(const int32_t* off, int32_t n_u, int64_t m, DevStatus* st) {
-    GRID_STRIDE(i, (int64_t)n_u + 1) {
-        int32_t o = off[i];
-        bool bad = (i == 0 && o != 0) || (i == n_u && (int64_t)o != m) || (i < n_u && off[i + 1] < o);
-        if (bad) flag_bad(st, kBadOffsets, &st->bad_offset, i);
-    }
+    GRID_STRIDE(i, (int64_t)n_u + 1) check_offset(off, n_u, m, i, st);
 }
 
 // The same per graph of a batch, one workgroup per graph; the reported
@@ -129,17 +131,20 @@ struct RowOrder {
     const uint32_t* off;
 };
 
-// Edge e of a single graph -> anchor id ea[e] and either pay[e] = centre id
-// | negative << 31 (the count) or ec[e] and en[e] (other users), with the
-// id-range and sign checks.  TOP: rows move to their rank's place instead,
-// ea = V id and pay = U rank | negative << 31 there (nothing is written once
-// the offsets are known to be malformed).
-template <bool TOP>
+// Edge e of a single graph, with the id-range and sign checks.  DEC_LISTS:
+// anchor id ea[e] and either pay[e] = centre id | negative << 31 (the count)
+// or ec[e] and en[e] (other users).  DEC_RANKED: rows move to their rank's
+// place, ea = V id and pay = U rank | negative << 31 there.  DEC_MATRIX: the
+// edge's byte of the cleared sign matrix becomes +1 or -1 (by a 32-bit atomic
+// OR, whose old value shows a repeated pair).  The last two write nothing once
+// the offsets are known to be malformed.
+enum { DEC_LISTS, DEC_RANKED, DEC_MATRIX };
+template <int MODE>
 __global__ __launch_bounds__(kDecThreads) void k_decode_single(const int32_t* off, const int32_t* adj,
                                                                const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
                                                                int s_is_u, int check_sign, DevStatus* st, uint32_t* ea,
-                                                               uint32_t* ec, uint8_t* en, uint32_t* pay, RowOrder ro) {
-    if (TOP && (*(volatile const int32_t*)&st->flags & kBadOffsets)) return;
+                                                               uint32_t* ec, uint8_t* en, uint32_t* pay, RowOrder ro, int64_t kpad) {
+    if (MODE != DEC_LISTS && (*(volatile const int32_t*)&st->flags & kBadOffsets)) return;
     __shared__ int32_t rr[2];
     __shared__ int32_t rowof[kDecChunk + kDecChunk / 16];
     __shared__ int32_t wmax[kDecThreads / kWave];
@@ -163,7 +168,15 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_single(const int32_t* of
         if (v < 0 || v >= n_v) flag_bad(st, kBadRange, &st->bad_range, e);
         if (check_sign && s != 1 && s != -1) flag_bad(st, kBadSign, &st->bad_sign, e);
         const uint32_t neg = s < 0 ? 1u : 0u;
-        if constexpr (TOP) {
+        if constexpr (MODE == DEC_MATRIX) {
+            if (v < 0 || v >= n_v) continue;
+            const int64_t at = s_is_u ? u * kpad + v : v * kpad + u;
+            const int sh = 8 * (int)(at & 3);
+            const uint32_t old = atomicOr(&ea[at >> 2], (neg ? 255u : 1u) << sh);
+            if ((old >> sh) & 255u) flag_bad(st, kBadDup, &st->bad_dup, e);
+            continue;
+        }
+        if constexpr (MODE == DEC_RANKED) {
             const uint32_t r = (uint32_t)ro.rank[u];
             const uint32_t p = ro.off[r] + (uint32_t)(e - off[u]);
             ea[p] = (uint32_t)v;
@@ -607,17 +620,36 @@ void launch_decode_single(const int32_t* off, const int32_t* adj, const int8_t* 
                           uint8_t* en, uint32_t* pay, hipStream_t s) {
     hipLaunchKernelGGL(k_check_offsets, dim3(grid_for((int64_t)n_u + 1, 256)), dim3(256), 0, s, off, n_u, m, st);
     if (m > 0)
-        hipLaunchKernelGGL(k_decode_single<false>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)), dim3(kDecThreads),
+        hipLaunchKernelGGL(k_decode_single<DEC_LISTS>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)), dim3(kDecThreads),
                            0, s, off, adj, sg, n_u, n_v, m, s_is_u, check_sign, st, ea, ec, en, pay,
-                           RowOrder{nullptr, nullptr});
+                           RowOrder{nullptr, nullptr}, (int64_t)0);
 }
 
 void top_decode(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
                 int check_sign, const int32_t* rank, const uint32_t* roff, DevStatus* st, uint32_t* key, uint32_t* pay,
                 hipStream_t s) {
-    hipLaunchKernelGGL(k_decode_single<true>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)), dim3(kDecThreads), 0,
-                       s, off, adj, sg, n_u, n_v, m, 1, check_sign, st, key, (uint32_t*)nullptr, (uint8_t*)nullptr,
-                       pay, RowOrder{rank, roff});
+    hipLaunchKernelGGL(k_decode_single<DEC_RANKED>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)),
+                       dim3(kDecThreads), 0, s, off, adj, sg, n_u, n_v, m, 1, check_sign, st, key, (uint32_t*)nullptr,
+                       (uint8_t*)nullptr, pay, RowOrder{rank, roff}, (int64_t)0);
+}
+
+// Offset checks and the cleared sign matrix (`bytes`, a multiple of 16).
+__global__ __launch_bounds__(256) void k_matrix_begin(const int32_t* off, int32_t n_u, int64_t m, uint4* mat,
+                                                      int64_t bytes, DevStatus* st) {
+    GRID_STRIDE(i, bytes / 16) mat[i] = uint4{0u, 0u, 0u, 0u};
+    GRID_STRIDE(i, (int64_t)n_u + 1) check_offset(off, n_u, m, i, st);
+}
+
+void launch_matrix_build(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
+                         int s_is_u, int check_sign, int8_t* mat, int64_t bytes, int64_t kpad, DevStatus* st,
+                         hipStream_t s) {
+    const int64_t items = bytes / 16 > n_u ? bytes / 16 : (int64_t)n_u + 1;
+    hipLaunchKernelGGL(k_matrix_begin, dim3(grid_for(items, 256)), dim3(256), 0, s, off, n_u, m,
+                       reinterpret_cast<uint4*>(mat), bytes, st);
+    hipLaunchKernelGGL(k_decode_single<DEC_MATRIX>, dim3((unsigned)((m + kDecChunk - 1) / kDecChunk)),
+                       dim3(kDecThreads), 0, s, off, adj, sg, n_u, n_v, m, s_is_u, check_sign, st,
+                       reinterpret_cast<uint32_t*>(mat), (uint32_t*)nullptr, (uint8_t*)nullptr, (uint32_t*)nullptr,
+                       RowOrder{nullptr, nullptr}, kpad);
 }
 
 void launch_decode_batched(const int32_t* off_cat, const int32_t* adj_cat, const int8_t* sg_cat, const DevGraph* gr,

@@ -117,25 +117,39 @@ constexpr int kDRowsPerPass = 256 * 16 / kDK;  // rows one pass of the workgroup
 // l % 32, row 8 * (i / 4) + 4 * (l / 32) + i % 4.
 __device__ __forceinline__ int mfma_row(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 
+// Adds a wave's wedges to the statistics (the matrix count walks none of them
+// one by one).
+__device__ __forceinline__ void add_wedges(uint32_t mine, DevStatus* st) {
+    const unsigned long long w = wave_sum((unsigned long long)mine);
+    if (lane_id() == 0 && w) {
+        atomicAdd(&my_sums(st)->wedges, w);
+        atomicAdd(&my_sums(st)->walked, w);
+    }
+}
+
 // One TILE x TILE output tile of the upper triangle of a block product per
 // workgroup, operands staged through registers into two LDS buffers
 // (TILE = 64: four waves of 32 x 32, one MFMA tile each; the 64-row tile
 // option runs this kernel, the 128-row default runs k_dense_lds below).
-template <int TILE>
+// ONE: the whole graph is the one block `one` (matrix count), the tile is the
+// workgroup's place in a square grid, and the pair terms and wedges are summed
+// with no table written.
+template <int TILE, bool ONE>
 __global__ __launch_bounds__(256, TILE == 128 ? 2 : 4) void k_dense(const DevBlock* __restrict__ blocks,
                                                                     const DevTile* __restrict__ tiles,
                                                                     const int8_t* __restrict__ mats,
-                                                                    uint32_t* __restrict__ tabs, DevStatus* st) {
+                                                                    uint32_t* __restrict__ tabs, DevStatus* st,
+                                                                    DevBlock one) {
     constexpr int WT = TILE / 2;           // wave tile edge
     constexpr int NT = WT / 32;            // MFMA tiles per wave tile edge
     constexpr int kLoads = TILE / kDRowsPerPass;  // 16-byte loads per thread and matrix per stage
-    if (status_bad(st)) return;
+    if (status_bad(st) || (ONE && blockIdx.x < blockIdx.y)) return;
     // two LDS stages: the next K slice is stored into one while the other
     // feeds the matrix cores
     __shared__ __align__(16) int8_t As[2][TILE * kDRow];
     __shared__ __align__(16) int8_t Bs[2][TILE * kDRow];
-    const DevTile T = tiles[blockIdx.x];
-    const DevBlock B = blocks[T.blk];
+    const DevTile T = ONE ? DevTile{0, (int32_t)blockIdx.y, (int32_t)blockIdx.x, 0} : tiles[blockIdx.x];
+    const DevBlock B = ONE ? one : blocks[T.blk];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const int wr = wave >> 1, wc = wave & 1;
     // on a diagonal tile the lower-left wave's outputs all lie below the
@@ -214,7 +228,8 @@ __global__ __launch_bounds__(256, TILE == 128 ? 2 : 4) void k_dense(const DevBlo
     // epilogue: pair terms of the upper triangle and the (a, b) table;
     // a, b <= 65535, so a (a - 1) / 2 fits 32 bits
     unsigned long long acc = 0;
-    uint32_t* tab = tabs + B.tab_off;
+    uint32_t wedges = 0;  // at most 2^6 outputs of this lane, each below 2^16
+    uint32_t* tab = ONE ? nullptr : tabs + B.tab_off;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -227,12 +242,14 @@ __global__ __launch_bounds__(256, TILE == 128 ? 2 : 4) void k_dense(const DevBlo
                     const uint32_t P = (uint32_t)accP[i][j][e], D = (uint32_t)accD[i][j][e];
                     const uint32_t a = (P + D) >> 1, b = (P - D) >> 1;
                     acc += (unsigned long long)(a * (a - (a > 0u))) + b * (b - (b > 0u));  // twice the pair terms
-                    tab[(int64_t)gu * B.rpad + gw] = a | (b << 16);
+                    if constexpr (ONE) wedges += P;
+                    else tab[(int64_t)gu * B.rpad + gw] = a | (b << 16);
                 }
             }
         }
     acc = wave_sum(acc);
     if (lane == 0 && acc) atomicAdd(&my_sums(st)->total, acc);
+    if constexpr (ONE) add_wedges(wedges, st);
 }
 
 // The 128 x 128 tile with operands loaded straight into LDS
@@ -266,10 +283,12 @@ __device__ __forceinline__ void wait_vm() {
 // workgroups, eight waves per CU) measured faster than eight of 64 x 32
 // (four waves per SIMD, but half the reuse of each fragment read).
 constexpr int kQWaves = 4;
+template <bool ONE>
 __global__ __launch_bounds__(kQWaves * kWave, 2) void k_dense_lds(const DevBlock* __restrict__ blocks,
                                                                  const DevTile* __restrict__ tiles,
                                                                  const int8_t* __restrict__ mats,
-                                                                 uint32_t* __restrict__ tabs, DevStatus* st) {
+                                                                 uint32_t* __restrict__ tabs, DevStatus* st,
+                                                                 DevBlock one) {
     constexpr int NWAVE = kQWaves;
     constexpr int WC = NWAVE / 2;                 // wave columns
     constexpr int WTR = kQTile / 2, WTC = kQTile / WC;  // wave tile rows, columns
@@ -278,14 +297,14 @@ __global__ __launch_bounds__(kQWaves * kWave, 2) void k_dense_lds(const DevBlock
     constexpr int LPM = RPW / 16;                  // loads per wave, matrix and stage
     constexpr int kInFlight = 2 * 2 * LPM;         // loads of the two stages after the one waited for
     typedef __attribute__((address_space(3))) void lds_t;
-    if (status_bad(st)) return;
+    if (status_bad(st) || (ONE && blockIdx.x < blockIdx.y)) return;
     // one LDS object per stage and matrix: the compiler then sees that a
     // stage's loads do not touch the stage being read and adds no wait of
     // its own (the waits below are the ones needed)
     __shared__ __align__(1024) int8_t A0[kQStageBytes], A1[kQStageBytes], A2[kQStageBytes], A3[kQStageBytes];
     __shared__ __align__(1024) int8_t B0[kQStageBytes], B1[kQStageBytes], B2[kQStageBytes], B3[kQStageBytes];
-    const DevTile T = tiles[blockIdx.x];
-    const DevBlock B = blocks[T.blk];
+    const DevTile T = ONE ? DevTile{0, (int32_t)blockIdx.y, (int32_t)blockIdx.x, 0} : tiles[blockIdx.x];
+    const DevBlock B = ONE ? one : blocks[T.blk];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const int wr = wave / WC, wc = wave % WC;
     // on a diagonal tile a wave whose outputs all lie below the diagonal
@@ -383,7 +402,8 @@ __global__ __launch_bounds__(kQWaves * kWave, 2) void k_dense_lds(const DevBlock
     if (idle) return;
 
     unsigned long long acc = 0;
-    uint32_t* tab = tabs + B.tab_off;
+    uint32_t wedges = 0;  // at most 2^6 outputs of this lane, each below 2^16
+    uint32_t* tab = ONE ? nullptr : tabs + B.tab_off;
 #pragma unroll
     for (int i = 0; i < NTR; ++i)
 #pragma unroll
@@ -396,12 +416,14 @@ __global__ __launch_bounds__(kQWaves * kWave, 2) void k_dense_lds(const DevBlock
                     const uint32_t P = (uint32_t)accP[i][j][e], D = (uint32_t)accD[i][j][e];
                     const uint32_t a = (P + D) >> 1, b = (P - D) >> 1;
                     acc += (unsigned long long)(a * (a - (a > 0u))) + b * (b - (b > 0u));  // twice the pair terms
-                    tab[(int64_t)gu * B.rpad + gw] = a | (b << 16);
+                    if constexpr (ONE) wedges += P;
+                    else tab[(int64_t)gu * B.rpad + gw] = a | (b << 16);
                 }
             }
         }
     acc = wave_sum(acc);
     if (lane == 0 && acc) atomicAdd(&my_sums(st)->total, acc);
+    if constexpr (ONE) add_wedges(wedges, st);
 }
 
 // ------------------------------------------------------------ host launchers
@@ -437,10 +459,28 @@ void launch_dense(const DevBlock* blocks, const DevTile* tiles, int32_t n_tiles,
                   DevStatus* st, int tile, hipStream_t s) {
     if (n_tiles <= 0) return;
     if (tile == 64)
-        hipLaunchKernelGGL(k_dense<64>, dim3((unsigned)n_tiles), dim3(256), 0, s, blocks, tiles, mats, tabs, st);
+        hipLaunchKernelGGL((k_dense<64, false>), dim3((unsigned)n_tiles), dim3(256), 0, s, blocks, tiles, mats, tabs,
+                           st, DevBlock{});
     else
-        hipLaunchKernelGGL(k_dense_lds, dim3((unsigned)n_tiles), dim3(kQWaves * kWave), 0, s, blocks, tiles, mats, tabs,
-                           st);
+        hipLaunchKernelGGL(k_dense_lds<false>, dim3((unsigned)n_tiles), dim3(kQWaves * kWave), 0, s, blocks, tiles,
+                           mats, tabs, st, DevBlock{});
+}
+
+// The pairs of the rows of one sign matrix [rpad][kpad] (n_r rows used):
+// rpad a multiple of tile, kpad of 64, at most 65535 columns used.
+void launch_matrix_pairs(const int8_t* mat, int32_t n_r, int32_t rpad, int32_t kpad, int tile, DevStatus* st,
+                         hipStream_t s) {
+    DevBlock one{};
+    one.n_r = n_r;
+    one.rpad = rpad;
+    one.kpad = kpad;
+    const unsigned t = (unsigned)(rpad / tile);
+    if (tile == 64)
+        hipLaunchKernelGGL((k_dense<64, true>), dim3(t, t), dim3(256), 0, s, (const DevBlock*)nullptr,
+                           (const DevTile*)nullptr, mat, (uint32_t*)nullptr, st, one);
+    else
+        hipLaunchKernelGGL(k_dense_lds<true>, dim3(t, t), dim3(kQWaves * kWave), 0, s, (const DevBlock*)nullptr,
+                           (const DevTile*)nullptr, mat, (uint32_t*)nullptr, st, one);
 }
 
 }  // namespace bbc

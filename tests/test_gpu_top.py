@@ -24,6 +24,7 @@ def ctx():
 
 def gpu(ctx, g, **kw):
     off, adj, sg = bbc.graph_tensors(g, "cuda:0")
+    kw.setdefault("queue_chunk", 1)  # a knob of the walk: small graphs are counted by matrix products without one
     return ctx.count(off, adj, sg, g.n_v, opts=bbc.options(**kw))
 
 
