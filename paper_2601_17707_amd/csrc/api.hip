@@ -414,6 +414,7 @@ struct TopPlan {
         t.e = c.take<uint32_t>(6 * m);
         t.icnt = c.take<uint32_t>(n);
         t.ioff = c.take<uint32_t>(n + 1);
+        t.row = c.take<uint2>(n);
         t.idx = c.take<uint32_t>(2 * m + (kTopFewBands + 1) * n);
         const int64_t hs = (int64_t)radix_hist_size(std::max(m, n));
         hist = c.take<uint32_t>(hs);
@@ -474,9 +475,10 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
     // heaviest vertices spread over the chip
     while (lw > 9 && ((int64_t)16 << lw) > n_max) --lw;
     top_vertices(T.degr, T.cstart, nu, nv, J.s_is_u ? 1 : 0, lw, T.thr, T.kx, T.work, T.bands, T.tc, st, s);
-    top_index(T.off, T.ent, xkey, e[4], m, nu, n, T.bands, T.icnt, T.ioff, T.idx, P.partials, st, s);
+    top_index(T.off, nu, n, T.bands, T.icnt, T.ioff, T.row, P.partials, st, s);
     uint32_t* mbase = e[1];  // and e[2]
-    top_work(xkey, e[4], T.ent, T.cross, T.off, T.thr, T.ioff, m, (int32_t)nu, T.mstart, mbase, T.kx, T.work, st, s);
+    top_work(xkey, e[4], T.ent, T.cross, T.row, T.thr, T.bands, m, (int32_t)nu, T.idx, T.mstart, mbase, T.kx, T.work,
+             st, s);
     top_schedule(T.work, T.kx, nu, n, (uint32_t)J.light_w, T.key, st, s);
     radix_sort_to(T.key, SortBufs{}, SortBufs{}, nullptr, nullptr, true, 0u, SortBufs{T.vk_a, nullptr, T.order},
                   nullptr, n, 0, 8, P.hist, P.hist_scan, P.partials, s);

@@ -106,6 +106,7 @@ struct TopBuild {
     uint32_t* cstart;
     TopBands* bands;
     uint32_t *ent, *cross, *mstart, *e, *idx;
+    uint2* row;
     TopCounts* tc;
 };
 
@@ -123,11 +124,10 @@ void top_move(const uint32_t* key, const uint32_t* pay, int64_t m, const uint32_
 void top_vertices(const uint32_t* degr, const uint32_t* cstart, int64_t n_u, int64_t n_v, int s_is_u, int lw,
                   uint32_t* thr, uint32_t* kx, unsigned long long* work, TopBands* bands, TopCounts* tc, DevStatus* st,
                   hipStream_t s);
-void top_index(const uint32_t* off, const uint32_t* ent, const uint32_t* xkey, const uint32_t* vpay, int64_t m,
-               int64_t n_u, int64_t n, const TopBands* bands, uint32_t* icnt, uint32_t* ioff, uint32_t* idx,
-               uint32_t* partials, const DevStatus* st, hipStream_t s);
-void top_work(const uint32_t* xkey, const uint32_t* vpay, const uint32_t* ent, const uint32_t* cross,
-              const uint32_t* off, const uint32_t* thr, const uint32_t* ioff, int64_t m, int32_t n_u, uint32_t* mstart,
+void top_index(const uint32_t* off, int64_t n_u, int64_t n, const TopBands* bands, uint32_t* icnt, uint32_t* ioff,
+               uint2* row, uint32_t* partials, const DevStatus* st, hipStream_t s);
+void top_work(const uint32_t* xkey, const uint32_t* vpay, const uint32_t* ent, const uint32_t* cross, const uint2* row,
+              const uint32_t* thr, const TopBands* bands, int64_t m, int32_t n_u, uint32_t* idx, uint32_t* mstart,
               uint32_t* mbase, uint32_t* kx, unsigned long long* work, const DevStatus* st, hipStream_t s);
 void top_schedule(const unsigned long long* work, const uint32_t* kx, int64_t n_u, int64_t n, uint32_t light_w,
                   uint32_t* skey, const DevStatus* st, hipStream_t s);

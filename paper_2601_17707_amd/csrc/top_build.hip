@@ -220,106 +220,111 @@ __device__ __forceinline__ uint32_t list_of(const uint32_t* xkey, const uint32_t
     return p < m ? top_rank(xkey[p]) : n_u + top_rank(vpay[p - m]);
 }
 
-__global__ void k_top_idx_fill(const uint32_t* __restrict__ xkey, const uint32_t* __restrict__ vpay,
-                               const uint32_t* __restrict__ ent, int64_t m, int64_t n_u,
-                               const TopBands* __restrict__ bands, const uint32_t* __restrict__ ioff,
-                               uint32_t* __restrict__ idx, const DevStatus* st) {
+// What a list's users need of it, in one 8-byte word: its start and its index
+// row (kNoIndex without one).
+__global__ void k_top_rows(const uint32_t* __restrict__ off, const uint32_t* __restrict__ ioff, int64_t n,
+                           uint2* __restrict__ row, const DevStatus* st) {
     if (top_bad(st)) return;
-    const TopBands BU = bands[0], BV = bands[1];
-    TOP_STRIDE(p, 2 * m) {
-        const bool lu = p < m;
-        const uint32_t y = list_of(xkey, vpay, m, (uint32_t)n_u, p);
-        const bool start = p == 0 || list_of(xkey, vpay, m, (uint32_t)n_u, p - 1) != y;
-        const bool end = p == 2 * m - 1 || list_of(xkey, vpay, m, (uint32_t)n_u, p + 1) != y;
-        const int32_t b = lu ? band_of(BV, (int32_t)top_rank(ent[p])) : band_of(BU, (int32_t)top_rank(ent[p]));
-        int32_t bp = -1;
-        if (!start) bp = lu ? band_of(BV, (int32_t)top_rank(ent[p - 1])) : band_of(BU, (int32_t)top_rank(ent[p - 1]));
-        if (b == bp && !end) continue;
-        const uint32_t i0 = ioff[y];
-        if (ioff[y + 1] == i0) continue;
-        for (int32_t k = bp + 1; k <= b; ++k) idx[i0 + k] = (uint32_t)p;
-        if (end) {
-            const int32_t nb = lu ? BV.nb : BU.nb;
-            for (int32_t k = b + 1; k <= nb; ++k) idx[i0 + k] = (uint32_t)(p + 1);
-        }
-    }
+    TOP_STRIDE(y, n) row[y] = uint2{off[y], ioff[y + 1] != ioff[y] ? ioff[y] : kNoIndex};
 }
 
 // ------------------------------------------------------------------- work
 
-// Per list entry p of vertex x that is a middle of x: mstart[p] = start of
-// the middle's list, mbase[p] = its index row (kNoIndex without one), and its
-// wedges, cross[p] - mstart[p], added to work[x]; kx[x] = number of middles.
-// Whole waves take 64 consecutive entries: prefix sums over the lanes and one
-// atomic per vertex and wave.
+// Per list entry p of vertex x: the index entries of x's list between the
+// bands of entry p - 1 and entry p; and if p is a middle of x: mstart[p] =
+// start of the middle's list, mbase[p] = its index row, and its wedges,
+// cross[p] - mstart[p], added to work[x]; kx[x] = number of middles.  Whole
+// waves take 64 consecutive entries: neighbours from the lanes beside, prefix
+// sums over the lanes and one atomic per vertex and wave.  Bound by the random
+// read per middle (20M power-law edges: one 8-byte row instead of three words
+// from two arrays, and the index filled on the way instead of by a kernel of
+// its own that read the entries again: 619 us instead of 558 + 270 us).
 __global__ __launch_bounds__(256) void k_top_work(const uint32_t* __restrict__ xkey, const uint32_t* __restrict__ vpay,
                                                   const uint32_t* __restrict__ ent, const uint32_t* __restrict__ cross,
-                                                  const uint32_t* __restrict__ off, const uint32_t* __restrict__ thr,
-                                                  const uint32_t* __restrict__ ioff, int64_t m, int32_t n_u,
-                                                  uint32_t* __restrict__ mstart, uint32_t* __restrict__ mbase,
-                                                  uint32_t* __restrict__ kx, unsigned long long* __restrict__ work,
-                                                  const DevStatus* st) {
+                                                  const uint2* __restrict__ row, const uint32_t* __restrict__ thr,
+                                                  const TopBands* __restrict__ bands, int64_t m, int32_t n_u,
+                                                  uint32_t* __restrict__ idx, uint32_t* __restrict__ mstart,
+                                                  uint32_t* __restrict__ mbase, uint32_t* __restrict__ kx,
+                                                  unsigned long long* __restrict__ work, const DevStatus* st) {
     if (top_bad(st)) return;
     constexpr int U = 4;  // entries per thread whose loads are in flight together
+    constexpr uint32_t kNone = 0xffffffffu;
     const int lane = lane_id();
+    const TopBands BU = bands[0], BV = bands[1];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x * U;
     for (int64_t p0 = (int64_t)blockIdx.x * blockDim.x * U; p0 < 2 * m; p0 += stride) {
-        uint32_t x[U], e[U], cr[U], s[U], ib[U];
+        uint32_t x[U], e[U], cr[U], xs[U], es[U];
         bool mid[U];
+        uint2 r[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t p = p0 + u * blockDim.x + threadIdx.x;
-            x[u] = 0xffffffffu;
-            e[u] = cr[u] = 0;
+            x[u] = xs[u] = kNone;
+            e[u] = cr[u] = es[u] = 0;
             if (p < 2 * m) {
                 x[u] = list_of(xkey, vpay, m, (uint32_t)n_u, p);
                 e[u] = ent[p];
                 cr[u] = cross[p];
             }
+            // the entries beside the wave's: before its first lane, after its last
+            const int64_t q = lane == 0 ? p - 1 : p + 1;
+            if ((lane == 0 || lane == kWave - 1) && q >= 0 && q < 2 * m) {
+                xs[u] = list_of(xkey, vpay, m, (uint32_t)n_u, q);
+                es[u] = ent[q];
+            }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) mid[u] = x[u] != 0xffffffffu && top_rank(e[u]) < thr[x[u]];
+        for (int u = 0; u < U; ++u) mid[u] = x[u] != kNone && top_rank(e[u]) < thr[x[u]];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            s[u] = 0;
-            ib[u] = kNoIndex;
-            if (mid[u]) {
-                const uint32_t y = (x[u] < (uint32_t)n_u ? (uint32_t)n_u : 0u) + top_rank(e[u]);
-                s[u] = off[y];
-                if (ioff[y + 1] != ioff[y]) ib[u] = ioff[y];
-            }
+            r[u] = uint2{0u, 0u};
+            if (mid[u]) r[u] = row[(x[u] < (uint32_t)n_u ? (uint32_t)n_u : 0u) + top_rank(e[u])];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t p = p0 + u * blockDim.x + threadIdx.x;
-            const uint32_t w = mid[u] ? cr[u] - s[u] : 0u;
+            const uint32_t w = mid[u] ? cr[u] - r[u].x : 0u;
             if (mid[u]) {
-                mstart[p] = s[u];
-                mbase[p] = ib[u];
+                mstart[p] = r[u].x;
+                mbase[p] = r[u].y;
             }
-            // does the next entry belong to x's middles too?
-            uint32_t xn = (uint32_t)__shfl_down((int)x[u], 1, kWave);
+            const bool lu = x[u] < (uint32_t)n_u;
+            const TopBands& B = lu ? BV : BU;
+            uint32_t xp = (uint32_t)__shfl_up((int)x[u], 1, kWave), xn = (uint32_t)__shfl_down((int)x[u], 1, kWave);
+            uint32_t ep = (uint32_t)__shfl_up((int)e[u], 1, kWave);
             int mn = __shfl_down((int)mid[u], 1, kWave);
+            if (lane == 0) {
+                xp = xs[u];
+                ep = es[u];
+            }
             if (lane == kWave - 1) {
-                xn = 0xffffffffu;
-                mn = 0;
-                if (mid[u] && p + 1 < 2 * m) {
-                    xn = list_of(xkey, vpay, m, (uint32_t)n_u, p + 1);
-                    mn = xn == x[u] && top_rank(ent[p + 1]) < thr[xn];
+                xn = xs[u];
+                mn = mid[u] && xn == x[u] && top_rank(es[u]) < thr[x[u]];
+            }
+            if (x[u] != kNone && B.nb > 1) {
+                const bool start = xp != x[u], end = xn != x[u];
+                const int32_t b = band_of(B, (int32_t)top_rank(e[u]));
+                const int32_t bp = start ? -1 : band_of(B, (int32_t)top_rank(ep));
+                if (b != bp || end) {
+                    const uint32_t i0 = row[x[u]].y;
+                    if (i0 != kNoIndex) {
+                        for (int32_t k = bp + 1; k <= b; ++k) idx[i0 + k] = (uint32_t)p;
+                        if (end)
+                            for (int32_t k = b + 1; k <= B.nb; ++k) idx[i0 + k] = (uint32_t)(p + 1);
+                    }
                 }
             }
-            if (mid[u] && (xn != x[u] || !mn)) kx[x[u]] = (uint32_t)(p + 1) - off[x[u]];
+            if (mid[u] && (xn != x[u] || !mn)) kx[x[u]] = (uint32_t)(p + 1) - row[x[u]].x;
             // inclusive sums over the lanes in two halves of 16 bits, then
             // the difference over each run of one vertex at its last lane
             const uint32_t lo = wave_inclusive_sum_dpp(w & 0xffffu), hi = wave_inclusive_sum_dpp(w >> 16);
-            const uint32_t xp = (uint32_t)__shfl_up((int)x[u], 1, kWave);
             const unsigned long long heads = __ballot(lane == 0 || xp != x[u]);
             const int h = 63 - __clzll(heads & (~0ull >> (63 - lane)));
             const uint32_t plo = (uint32_t)__shfl((int)lo, h > 0 ? h - 1 : 0, kWave);
             const uint32_t phi = (uint32_t)__shfl((int)hi, h > 0 ? h - 1 : 0, kWave);
             const unsigned long long run = ((unsigned long long)(hi - (h > 0 ? phi : 0u)) << 16) + (lo - (h > 0 ? plo : 0u));
             const bool last = lane == kWave - 1 || ((heads >> (lane + 1)) & 1ull);
-            if (x[u] != 0xffffffffu && last && run) atomicAdd(&work[x[u]], run);
+            if (x[u] != kNone && last && run) atomicAdd(&work[x[u]], run);
         }
     }
 }
@@ -396,20 +401,18 @@ void top_vertices(const uint32_t* degr, const uint32_t* cstart, int64_t n_u, int
                        s_is_u, lw, thr, kx, work, bands, tc, st);
 }
 
-void top_index(const uint32_t* off, const uint32_t* ent, const uint32_t* xkey, const uint32_t* vpay, int64_t m,
-               int64_t n_u, int64_t n, const TopBands* bands, uint32_t* icnt, uint32_t* ioff, uint32_t* idx,
-               uint32_t* partials, const DevStatus* st, hipStream_t s) {
+void top_index(const uint32_t* off, int64_t n_u, int64_t n, const TopBands* bands, uint32_t* icnt, uint32_t* ioff,
+               uint2* row, uint32_t* partials, const DevStatus* st, hipStream_t s) {
     hipLaunchKernelGGL(k_top_idx_count, dim3(top_grid(n, 256)), dim3(256), 0, s, off, n_u, n, bands, icnt, st);
     scan_exclusive_u32(icnt, ioff, n, partials, s);
-    hipLaunchKernelGGL(k_top_idx_fill, dim3(top_grid(2 * m, 256)), dim3(256), 0, s, xkey, vpay, ent, m, n_u, bands,
-                       (const uint32_t*)ioff, idx, st);
+    hipLaunchKernelGGL(k_top_rows, dim3(top_grid(n, 256)), dim3(256), 0, s, off, ioff, n, row, st);
 }
 
-void top_work(const uint32_t* xkey, const uint32_t* vpay, const uint32_t* ent, const uint32_t* cross,
-              const uint32_t* off, const uint32_t* thr, const uint32_t* ioff, int64_t m, int32_t n_u, uint32_t* mstart,
+void top_work(const uint32_t* xkey, const uint32_t* vpay, const uint32_t* ent, const uint32_t* cross, const uint2* row,
+              const uint32_t* thr, const TopBands* bands, int64_t m, int32_t n_u, uint32_t* idx, uint32_t* mstart,
               uint32_t* mbase, uint32_t* kx, unsigned long long* work, const DevStatus* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_top_work, dim3(top_grid((2 * m + 3) / 4, 256, 2048)), dim3(256), 0, s, xkey, vpay, ent, cross,
-                       off, thr, ioff, m, n_u, mstart, mbase, kx, work, st);
+    hipLaunchKernelGGL(k_top_work, dim3(top_grid(2 * m, 1024, 2048)), dim3(256), 0, s, xkey, vpay, ent, cross, row, thr,
+                       bands, m, n_u, idx, mstart, mbase, kx, work, st);
 }
 
 void top_schedule(const unsigned long long* work, const uint32_t* kx, int64_t n_u, int64_t n, uint32_t light_w,
