@@ -452,7 +452,7 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
 
     // V lists: stable by V id, then to rank order
     const int bits_v = bits_for((uint64_t)(nv - 1)), bits_u = bits_for((uint64_t)(nu - 1));
-    const bool odd1 = m <= 4096 || (radix_passes(bits_v) & 1);
+    const bool odd1 = m <= 4096 || (radix_passes(bits_v, m) & 1);
     uint32_t *sk = odd1 ? e[2] : e[0], *sp = odd1 ? e[3] : e[1];
     radix_sort_to(e[0], SortBufs{e[2], e[3], nullptr}, SortBufs{e[0], e[1], nullptr}, e[1], nullptr, false, 0u,
                   SortBufs{sk, sp, nullptr}, nullptr, m, 0, bits_v, P.hist, P.hist_scan, P.partials, s);
@@ -462,7 +462,7 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
     top_move(sk, sp, m, T.first, T.rank, T.off + nu, T.ent + m, e[4], st, s);
     // U lists: stable by U rank (the V lists' entries without their sign), with both
     // directions of the cross positions
-    const int np = radix_passes(bits_u);
+    const int np = radix_passes(bits_u, m);
     uint32_t* xkey = (m > 4096 && np >= 3 && (np & 1)) ? e[0] : e[3];
     radix_sort_to(T.ent + m, SortBufs{e[0], e[1], e[2]}, SortBufs{e[3], e[5], T.mstart}, e[4], nullptr, true,
                   (uint32_t)m, SortBufs{xkey, T.ent, T.cross}, reinterpret_cast<int32_t*>(T.cross), m, 0, bits_u, P.hist,

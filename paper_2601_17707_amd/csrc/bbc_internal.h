@@ -239,15 +239,14 @@ void radix_sort(const uint32_t* k_in, uint32_t* k_a, uint32_t* k_b, const uint32
                 const uint32_t** v0_out, const uint32_t** v1_out, int32_t* inv_out = nullptr);
 
 // The same sort with every destination named: stable, on bits
-// [shift0, shift0 + bits) of the keys, passes of 8 bits (radix_passes(bits)
-// of them) going through a, b, a, ... and the last one to `out`, which may
+// [shift0, shift0 + bits) of the keys, radix_passes(bits, n) passes going through a, b, a, ... and the last one to `out`, which may
 // share memory with whichever of the inputs, a or b that pass does not read.
 // With v1_iota payload 1 is iota0 + the input index; out.v1 may be NULL when
 // inv_out is given.
 struct SortBufs {
     uint32_t *k, *v0, *v1;
 };
-int radix_passes(int bits);
+int radix_passes(int bits, int64_t n);
 void radix_sort_to(const uint32_t* k_in, const SortBufs& a, const SortBufs& b, const uint32_t* v0_in,
                    const uint32_t* v1_in, bool v1_iota, uint32_t iota0, const SortBufs& out, int32_t* inv_out,
                    int64_t n, int shift0, int bits, uint32_t* hist, uint32_t* hist_scan, uint32_t* partials,

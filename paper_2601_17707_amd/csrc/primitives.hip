@@ -1,5 +1,7 @@
 // Device-wide building blocks: fills, exclusive scan and a stable LSD radix
 // sort, used to build the degree-ordered CSR on the GPU.
+#include <type_traits>
+
 #include "bbc_internal.h"
 
 namespace bbc {
@@ -135,18 +137,47 @@ void scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* 
 
 // ------------------------------------------------------------- radix sort
 
-constexpr int kRsThreads = 256;  // one thread per digit value
-constexpr int kRsRounds = 16;
-constexpr int kRsTile = kRsThreads * kRsRounds;
-constexpr int kRsWaves = kRsThreads / kWave;
+// Shape of the multi-tile passes for digits of DB bits: one thread per digit
+// value, a tile of kRounds items per thread (with wider digits the tile grows
+// along, so that a digit's run in a tile keeps its length and the histograms
+// their size).
+template <int DB>
+struct RsShape {
+    static constexpr int kDigits = 1 << DB;
+    static constexpr int kThreads = kDigits;
+    static constexpr int kRounds = DB == 8 ? 16 : 17;
+    static constexpr int kTile = kThreads * kRounds;
+    static constexpr int kWaves = kThreads / kWave;
+};
+constexpr int kRsTile = RsShape<8>::kTile;
+// one-tile sorts: the same tile on four times the threads
+constexpr int kRsOneThreads = 1024;
 
 size_t radix_hist_size(int64_t n) { return (size_t)256 * (size_t)((n + kRsTile - 1) / kRsTile) + 1; }
 
-int radix_passes(int bits) { return bits < 1 ? 1 : (bits + 7) / 8; }
+// Digit width of a sort.  Every pass moves all items once (near the rate of a
+// copy on large sorts), so digits of 9 or 10 bits are taken where they save a
+// pass: 17 to 20 bits in two passes, 25 to 30 in three.  20M items with 20-bit
+// keys: 230 us a pass of 10 bits and 150 us of 8, their histograms and scans
+// 45 and 40 us; 2M items with 17-bit keys: 33 and 22 us a pass.  Below kRsWideMin items their histograms (512 or 1024 counts
+// per tile of 8704 or 17408) would exceed radix_hist_size.
+constexpr int64_t kRsWideMin = 278528;
+static int radix_digit(int bits, int64_t n) {
+    const int p8 = (bits + 7) / 8, p10 = (bits + 9) / 10;
+    return n < kRsWideMin || p10 >= p8 ? 8 : (bits + p10 - 1) / p10;
+}
 
-// Mask of a pass's digit when `left` key bits remain (key bits above the
-// sorted ones may hold anything).
-__host__ __device__ __forceinline__ uint32_t radix_mask(int left) { return left >= 8 ? 255u : (1u << left) - 1u; }
+int radix_passes(int bits, int64_t n) {
+    if (bits < 1) bits = 1;
+    const int db = radix_digit(bits, n);
+    return (bits + db - 1) / db;
+}
+
+// Mask of a pass's digit of db bits when `left` key bits remain (key bits
+// above the sorted ones may hold anything).
+__host__ __device__ __forceinline__ uint32_t radix_mask(int left, int db) {
+    return left >= db ? (1u << db) - 1u : (1u << left) - 1u;
+}
 
 // Tile of workgroup b.  Workgroups are dealt round robin over the eight
 // XCDs, so XCD x = b % 8 is given a contiguous range of tiles: consecutive
@@ -157,12 +188,13 @@ __device__ __forceinline__ int64_t rs_tile(int64_t b, int64_t nblk) {
     return x * q + (x < r ? x : r) + i;
 }
 
-// Lanes of the wave holding the same 8-bit digit d (eight ballots), among
-// the lanes where valid is set.
+// Lanes of the wave holding the same digit d of DB bits (a ballot per bit),
+// among the lanes where valid is set.
+template <int DB>
 __device__ __forceinline__ unsigned long long digit_peers(uint32_t d, bool valid) {
     unsigned long long peers = __ballot(valid);
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
+    for (int bit = 0; bit < DB; ++bit) {
         const int on = (d >> bit) & 1u;
         const unsigned long long m = __ballot(on);
         peers &= on ? m : ~m;
@@ -170,13 +202,17 @@ __device__ __forceinline__ unsigned long long digit_peers(uint32_t d, bool valid
     return peers;
 }
 
-// Digit counts of one tile; hist is digit-major: hist[d * nblk + tile].
+// Digit counts of one tile; hist is digit-major (hist[d * nblk + tile]), or
+// with `rows` tile-major (hist[tile * digits + d]).
 // When every lane of a wave holds the same digit (the high digits of
 // narrow or grouped keys) one lane adds them all, instead of 64 atomics on
 // one LDS word.
-__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, int64_t n, int shift, uint32_t dmask,
-                                                        uint32_t* hist, int64_t nblk) {
-    __shared__ uint32_t h[256];
+template <int DB>
+__global__ __launch_bounds__(RsShape<DB>::kThreads) void k_rs_hist(const uint32_t* keys, int64_t n, int shift,
+                                                                   uint32_t dmask, uint32_t* hist, int64_t nblk,
+                                                                   int rows) {
+    constexpr int kRsThreads = RsShape<DB>::kThreads, kRsRounds = RsShape<DB>::kRounds, kRsTile = RsShape<DB>::kTile;
+    __shared__ uint32_t h[RsShape<DB>::kDigits];
     h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t tile = rs_tile(blockIdx.x, nblk);
@@ -195,14 +231,14 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, in
         }
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
+    hist[rows ? tile * RsShape<DB>::kDigits + threadIdx.x : (int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
 }
 
 // Stable scatter of one tile, staged through LDS so that global writes are
-// runs of consecutive positions.  Wave w owns the tile's items
-// [w * 1024, (w + 1) * 1024), visited in 16 rounds of 64, so the input
-// order is (wave, round, lane).  Within a round the lanes that share a
-// digit are found with eight ballots; an item's place among its wave's
+// runs of consecutive positions.  Each wave owns consecutive items of the
+// tile, visited in rounds of 64, so the input order is (wave, round, lane).
+// Within a round the lanes that share a digit are found with a ballot per
+// bit; an item's place among its wave's
 // items of that digit is the wave's running count of the digit plus the
 // number of such lanes below it (the lowest of them then advances the
 // count; a wave's LDS operations complete in order).  After one barrier
@@ -212,30 +248,50 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* keys, in
 // at its global offset (the digit of each place is kept in LDS for the
 // payloads).  Keys and places stay in registers between the phases; each
 // payload is read when its turn comes.  One buffer and few registers let
-// six tiles run per CU (26 KB of LDS each).  With inv_out,
+// six 8-bit tiles run per CU (26 KB of LDS each; wide digits: two of 512 or
+// one of 1024 threads).  Without hist_scan (few tiles) the histogram is
+// tile-major and every workgroup sums it itself: two launches a pass instead
+// of three to five, of 2 to 4 us each.  With inv_out,
 // inv_out[v1] receives the item's new position (the inverse of the
 // permutation that payload tracks); v1_out may then be NULL.
-__global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys, uint32_t* keys_out,
+template <int DB>
+__global__ __launch_bounds__(RsShape<DB>::kThreads) void k_rs_scatter(const uint32_t* keys, uint32_t* keys_out,
                                                            const uint32_t* v0, uint32_t* v0_out,
                                                            const uint32_t* v1, uint32_t* v1_out, int v1_iota,
                                                            uint32_t iota0, int32_t* inv_out, int64_t n, int shift,
                                                            uint32_t dmask,
                                                            const uint32_t* hist, const uint32_t* hist_scan,
                                                            int64_t nblk) {
+    constexpr int kRsThreads = RsShape<DB>::kThreads, kRsRounds = RsShape<DB>::kRounds, kRsTile = RsShape<DB>::kTile;
+    constexpr int kRsWaves = RsShape<DB>::kWaves, kDigits = RsShape<DB>::kDigits;
+    using Digit = std::conditional_t<DB == 8, uint8_t, uint16_t>;
+    using Count = std::conditional_t<DB == 8, uint32_t, uint16_t>;  // below kRsTile
     __shared__ uint32_t s_buf[kRsTile];
-    __shared__ uint8_t s_dig[kRsTile];
-    __shared__ uint32_t lstart[256];  // first place of each digit in the sorted tile
-    __shared__ uint32_t gstart[256];  // global position of that place
-    __shared__ uint32_t wcnt[kRsWaves][256];
-    __shared__ uint32_t scan_tmp[kRsWaves + 1];
+    __shared__ Digit s_dig[kRsTile];
+    __shared__ uint32_t lstart[kDigits];  // first place of each digit in the sorted tile
+    __shared__ uint32_t gstart[kDigits];  // global position of that place
+    __shared__ Count wcnt[kRsWaves][kDigits];
+    __shared__ uint32_t scan_tmp[kRsWaves + 1], scan_tmp2[kRsWaves + 1];
     const int t = threadIdx.x, w = t / kWave, lane = lane_id();
     // the inverse scatter's writes go anywhere: tiles in launch order there
     const int64_t tile = inv_out ? (int64_t)blockIdx.x : rs_tile(blockIdx.x, nblk);
-    const uint32_t cnt = hist[(int64_t)t * nblk + tile];
-    uint32_t tot;
+    uint32_t cnt, before = 0, all = 0, tot;
+    if (hist_scan) {
+        cnt = hist[(int64_t)t * nblk + tile];
+        before = hist_scan[(int64_t)t * nblk + tile];
+    } else {
+        cnt = hist[tile * kDigits + t];
+#pragma unroll 16
+        for (int j = 0; j < (int)nblk; ++j) {
+            const uint32_t c = hist[j * kDigits + t];
+            all += c;
+            before += j < (int)tile ? c : 0u;
+        }
+        before += block_exclusive_scan<kRsThreads>(all, scan_tmp2, &tot);
+    }
     const uint32_t ls = block_exclusive_scan<kRsThreads>(cnt, scan_tmp, &tot);
     lstart[t] = ls;
-    gstart[t] = hist_scan[(int64_t)t * nblk + tile];
+    gstart[t] = before;
 #pragma unroll
     for (int k = 0; k < kRsWaves; ++k) wcnt[k][t] = 0;
     __syncthreads();
@@ -254,11 +310,11 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
     for (int r = 0; r < kRsRounds; ++r) {
         const bool valid = base + (uint32_t)(r * kWave + lane) < n32;
         const uint32_t d = (key[r] >> shift) & dmask;
-        const unsigned long long peers = digit_peers(d, valid);
+        const unsigned long long peers = digit_peers<DB>(d, valid);
         const uint32_t rk = (uint32_t)__popcll(peers & below);
         const uint32_t run = wcnt[w][d];
         place[r] = run + rk;
-        if (valid && rk == 0) wcnt[w][d] = run + (uint32_t)__popcll(peers);
+        if (valid && rk == 0) wcnt[w][d] = (Count)(run + (uint32_t)__popcll(peers));
     }
     __syncthreads();
     {  // digit t: offset of each wave's places
@@ -266,7 +322,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
 #pragma unroll
         for (int k = 0; k < kRsWaves; ++k) {
             const uint32_t c = wcnt[k][t];
-            wcnt[k][t] = off;
+            wcnt[k][t] = (Count)off;
             off += c;
         }
     }
@@ -284,7 +340,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
     for (int r = 0; r < kRsRounds; ++r) {
         if (place[r] != 0xffffffffu) {
             s_buf[place[r]] = key[r];
-            s_dig[place[r]] = (uint8_t)((key[r] >> shift) & dmask);
+            s_dig[place[r]] = (Digit)((key[r] >> shift) & dmask);
         }
     }
     __syncthreads();
@@ -332,10 +388,12 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* keys,
 // (wave, round, lane) order the ranking uses, so each pass is stable as in
 // k_rs_scatter.  Used for the small sorts (per-anchor keys of small graphs),
 // where the launches of the multi-tile passes would dominate.
-__global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, uint32_t* keys_out,
+// Sixteen waves of four rounds (13.5 us as four of sixteen, 9.3 us so, 1980 items of 8 bits).
+__global__ __launch_bounds__(kRsOneThreads) void k_rs_single(const uint32_t* keys, uint32_t* keys_out,
                                                           const uint32_t* v0, uint32_t* v0_out, const uint32_t* v1,
                                                           uint32_t* v1_out, int v1_iota, uint32_t iota0,
                                                           int32_t* inv_out, int n, int shift0, int bits) {
+    constexpr int kRsThreads = kRsOneThreads, kRsRounds = kRsTile / kRsThreads, kRsWaves = kRsThreads / kWave;
     __shared__ uint32_t s_key[kRsTile];
     __shared__ uint32_t s_v0[kRsTile];
     __shared__ uint32_t s_v1[kRsTile];
@@ -351,7 +409,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
     const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
     const int base = w * (kRsRounds * kWave);
     for (int shift = shift0; shift < shift0 + bits; shift += 8) {
-        const uint32_t dmask = radix_mask(shift0 + bits - shift);
+        const uint32_t dmask = radix_mask(shift0 + bits - shift, 8);
         __syncthreads();  // the previous pass's items are in place
         uint32_t key[kRsRounds], a[kRsRounds], b[kRsRounds], place[kRsRounds];
 #pragma unroll
@@ -362,14 +420,13 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
             a[r] = (valid && with_v0) ? s_v0[i] : 0u;
             b[r] = (valid && with_v1) ? s_v1[i] : 0u;
         }
-#pragma unroll
-        for (int k = 0; k < kRsWaves; ++k) wcnt[k][t] = 0;
+        for (int k = t; k < kRsWaves * 256; k += kRsThreads) (&wcnt[0][0])[k] = 0;
         __syncthreads();  // every item read; counts cleared
 #pragma unroll
         for (int r = 0; r < kRsRounds; ++r) {
             const bool valid = base + r * kWave + lane < n;
             const uint32_t d = (key[r] >> shift) & dmask;
-            const unsigned long long peers = digit_peers(d, valid);
+            const unsigned long long peers = digit_peers<8>(d, valid);
             const uint32_t rk = (uint32_t)__popcll(peers & below);
             const uint32_t run = wcnt[w][d];
             place[r] = run + rk;
@@ -377,15 +434,19 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
         }
         __syncthreads();
         uint32_t c_all = 0;  // digit t over all waves
+        if (t < 256) {
 #pragma unroll
-        for (int k = 0; k < kRsWaves; ++k) c_all += wcnt[k][t];
+            for (int k = 0; k < kRsWaves; ++k) c_all += wcnt[k][t];
+        }
         uint32_t tot;
         uint32_t off = block_exclusive_scan<kRsThreads>(c_all, scan_tmp, &tot);
+        if (t < 256) {
 #pragma unroll
-        for (int k = 0; k < kRsWaves; ++k) {
-            const uint32_t c = wcnt[k][t];
-            wcnt[k][t] = off;
-            off += c;
+            for (int k = 0; k < kRsWaves; ++k) {
+                const uint32_t c = wcnt[k][t];
+                wcnt[k][t] = off;
+                off += c;
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -407,6 +468,24 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_single(const uint32_t* keys, 
     }
 }
 
+// Most tiles whose histogram every workgroup of the scatter sums itself.
+constexpr int64_t kRsFewTiles = 128;
+
+template <int DB>
+static void radix_pass(const uint32_t* ks, uint32_t* ko, const uint32_t* v0, uint32_t* v0o, const uint32_t* v1,
+                       uint32_t* v1o, int iota, uint32_t iota0, int32_t* inv_out, int64_t n, int shift, uint32_t dmask,
+                       uint32_t* hist, uint32_t* hist_scan, uint32_t* partials, hipStream_t s) {
+    using S = RsShape<DB>;
+    const int64_t nblk = (n + S::kTile - 1) / S::kTile;
+    const bool few = nblk <= kRsFewTiles;
+    hipLaunchKernelGGL(k_rs_hist<DB>, dim3((unsigned)nblk), dim3(S::kThreads), 0, s, ks, n, shift, dmask, hist, nblk,
+                       few ? 1 : 0);
+    if (!few) scan_exclusive_u32(hist, hist_scan, S::kDigits * nblk, partials, s);
+    hipLaunchKernelGGL(k_rs_scatter<DB>, dim3((unsigned)nblk), dim3(S::kThreads), 0, s, ks, ko, v0, v0o, v1, v1o, iota,
+                       iota0, inv_out, n, shift, dmask, (const uint32_t*)hist,
+                       few ? (const uint32_t*)nullptr : (const uint32_t*)hist_scan, nblk);
+}
+
 void radix_sort_to(const uint32_t* k_in, const SortBufs& a, const SortBufs& b, const uint32_t* v0_in,
                    const uint32_t* v1_in, bool v1_iota, uint32_t iota0, const SortBufs& out, int32_t* inv_out,
                    int64_t n, int shift0, int bits, uint32_t* hist, uint32_t* hist_scan, uint32_t* partials,
@@ -414,26 +493,23 @@ void radix_sort_to(const uint32_t* k_in, const SortBufs& a, const SortBufs& b, c
     if (n <= 0) return;
     if (bits < 1) bits = 1;
     const bool with_v1 = v1_iota || v1_in != nullptr;
-    const int64_t nblk = (n + kRsTile - 1) / kRsTile;
-    if (nblk == 1) {  // one tile: every pass in one launch
-        hipLaunchKernelGGL(k_rs_single, dim3(1), dim3(kRsThreads), 0, s, k_in, out.k, v0_in, v0_in ? out.v0 : nullptr,
-                           v1_in, with_v1 ? out.v1 : nullptr, v1_iota ? 1 : 0, iota0, inv_out, (int)n, shift0, bits);
+    if (n <= kRsTile) {  // one tile: every pass in one launch
+        hipLaunchKernelGGL(k_rs_single, dim3(1), dim3(kRsOneThreads), 0, s, k_in, out.k, v0_in,
+                           v0_in ? out.v0 : nullptr, v1_in, with_v1 ? out.v1 : nullptr, v1_iota ? 1 : 0, iota0,
+                           inv_out, (int)n, shift0, bits);
         return;
     }
-    const int n_pass = radix_passes(bits);
+    const int n_pass = radix_passes(bits, n), db = radix_digit(bits, n);
     const uint32_t *ks = k_in, *v0s = v0_in, *v1s = v1_in;
     int iota = v1_iota ? 1 : 0;
     for (int pass = 0; pass < n_pass; ++pass) {
         const bool last = pass == n_pass - 1;
         const SortBufs& d = last ? out : (pass & 1) ? b : a;
-        const int shift = shift0 + 8 * pass;
-        const uint32_t dmask = radix_mask(bits - 8 * pass);
-        hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nblk), dim3(kRsThreads), 0, s, ks, n, shift, dmask, hist, nblk);
-        scan_exclusive_u32(hist, hist_scan, 256 * nblk, partials, s);
-        hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nblk), dim3(kRsThreads), 0, s, ks, d.k, v0s,
-                           v0_in ? d.v0 : nullptr, v1s, with_v1 ? d.v1 : nullptr, iota, iota0,
-                           last ? inv_out : nullptr, n, shift, dmask, (const uint32_t*)hist, (const uint32_t*)hist_scan,
-                           nblk);
+        const int shift = shift0 + db * pass;
+        const uint32_t dmask = radix_mask(bits - db * pass, db);
+        auto* const run = db == 10 ? radix_pass<10> : db == 9 ? radix_pass<9> : radix_pass<8>;
+        run(ks, d.k, v0s, v0_in ? d.v0 : nullptr, v1s, with_v1 ? d.v1 : nullptr, iota, iota0,
+            last ? inv_out : nullptr, n, shift, dmask, hist, hist_scan, partials, s);
         ks = d.k;
         v0s = v0_in ? d.v0 : nullptr;
         v1s = d.v1;
@@ -449,7 +525,7 @@ void radix_sort(const uint32_t* k_in, uint32_t* k_a, uint32_t* k_b, const uint32
     // result lies in the buffer pair the last pass wrote (the inputs when
     // there is nothing to sort)
     const bool iota = v1_a != nullptr && v1_in == nullptr;
-    const bool odd = n <= kRsTile || (radix_passes(bits) & 1);
+    const bool odd = n <= kRsTile || (radix_passes(bits, n) & 1);
     const SortBufs a{k_a, v0_a, v1_a}, b{k_b, v0_b, v1_b};
     SortBufs out = odd ? a : b;
     if (inv_out) out.v1 = nullptr;
