@@ -12,10 +12,13 @@
  * sign (a) and disagree (b), and add C(a,2) + C(b,2).  Only pairs of agreeing
  * or pairs of disagreeing wedges close a balanced butterfly (Lemma 1), so no
  * unbalanced structure is ever formed.  Ranks follow the vertex priority of
- * Definition 6 (degree, then id).  Totals without dense blocks or per-vertex
- * output are counted from both sides where that walks fewer wedges: each
+ * Definition 6 (degree, then id).  Totals and per-vertex counts without dense
+ * blocks are counted from both sides where that walks fewer wedges: each
  * butterfly at its vertex of highest degree (class), from the wedges whose
- * middle and end lie below that vertex; the count is the same.  Every step runs in the library's own HIP
+ * middle and end lie below that vertex.  Totals of graphs whose signed
+ * adjacency matrix is small come from two int8 products of that matrix,
+ * unless an option that shapes the walk is set.  The counts are the same
+ * every way.  Every step runs in the library's own HIP
  * kernels on the caller's stream; counts are exact integers.
  *
  * Entry points: bbc_count (total, optional per-vertex counts and dense

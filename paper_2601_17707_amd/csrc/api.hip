@@ -406,6 +406,7 @@ struct TopPlan {
         t.first = c.take<uint32_t>(nv);
         t.last = c.take<uint32_t>(nv);
         t.work = c.take<unsigned long long>(n);
+        t.pv = c.take<unsigned long long>(J.pv ? n : 0);
         t.cstart = c.take<uint32_t>(2 * (kDegClasses + 1));
         t.bands = c.take<TopBands>(2);
         t.ent = c.take<uint32_t>(2 * m);
@@ -430,7 +431,7 @@ void top_rank_side(TopPlan& P, int64_t n, int side, int64_t x0, hipStream_t s) {
     TopBuild& T = P.t;
     radix_sort_to(T.key, SortBufs{}, SortBufs{}, nullptr, nullptr, true, 0u, SortBufs{T.vk_a, nullptr, T.vv_a}, nullptr,
                   n, 0, 8, P.hist, P.hist_scan, P.partials, s);
-    top_ranks(T.vv_a, T.deg, n, side, T.rank, T.degr + x0, T.cstart, s);
+    top_ranks(T.vv_a, T.deg, n, side, T.rank + x0, T.degr + x0, T.cstart, s);
 }
 
 // Queues the top-vertex pipeline on stream s (kernel launches only).
@@ -459,7 +460,7 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
     top_runs(sk, sp, m, nv, check_dup, T.first, T.last, T.deg, T.key, st, s);
     top_rank_side(P, nv, 1, nu, s);
     scan_exclusive_u32(T.degr + nu, T.off + nu, nv, P.partials, s, (uint32_t)m);
-    top_move(sk, sp, m, T.first, T.rank, T.off + nu, T.ent + m, e[4], st, s);
+    top_move(sk, sp, m, T.first, T.rank + nu, T.off + nu, T.ent + m, e[4], st, s);
     // U lists: stable by U rank (the V lists' entries without their sign), with both
     // directions of the cross positions
     const int np = radix_passes(bits_u, m);
@@ -479,15 +480,17 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
     uint32_t* mbase = e[1];  // and e[2]
     top_work(xkey, e[4], T.ent, T.cross, T.row, T.thr, T.bands, m, (int32_t)nu, T.idx, T.mstart, mbase, T.kx, T.work,
              st, s);
-    top_schedule(T.work, T.kx, nu, n, (uint32_t)J.light_w, T.key, st, s);
+    top_schedule(T.work, T.kx, nu, n, (uint32_t)(J.pv ? kLightMaxWork : J.light_w), T.key, st, s);
     radix_sort_to(T.key, SortBufs{}, SortBufs{}, nullptr, nullptr, true, 0u, SortBufs{T.vk_a, nullptr, T.order},
                   nullptr, n, 0, 8, P.hist, P.hist_scan, P.partials, s);
     top_counts(T.vk_a, n, T.tc, s);
     if (ev) (void)hipEventRecord(ev[1], s);
 
     const TopArgs a{T.ent,  T.cross, T.mstart, mbase, T.off, T.kx, T.order, T.idx, T.work, T.bands, st, T.tc, T.inv,
-                    (int32_t)nu, J.schedule == BBC_SCHED_STATIC ? 1 : 0, J.queue_chunk, J.light_chunk};
-    launch_top(J.top_words, J.top_wg, J.top_grid, J.light_grid, J.n_cu, a, s);
+                    T.pv, (int32_t)nu, J.schedule == BBC_SCHED_STATIC ? 1 : 0, J.queue_chunk, J.light_chunk};
+    if (J.pv) fill_bytes(T.pv, n * 8, s);
+    if (J.pv) launch_top_full(J.n_cu, a, T.rank, n, J.pv, s);
+    else launch_top(J.top_words, J.top_wg, J.top_grid, J.light_grid, J.n_cu, a, s);
     if (ev) (void)hipEventRecord(ev[2], s);
 }
 
@@ -682,16 +685,30 @@ void set_regimes(Job& J, const bbc_options& o, bool full) {
 // smaller sides get two narrower workgroups per CU.
 constexpr int kTopWords = 32768, kTopWG = 1024, kTopSmallWords = 16384, kTopSmallWG = 512;
 
+// Whether a per-vertex count takes the top-vertex pipeline: its launches and
+// second readings pay from 60K edges, and on a smaller side of 5000 to 32767
+// vertices (at most two of the one-sided walk's wide bands) only up to a mean
+// degree of 70 over both sides.  us, one-sided and top-vertex: 313 and 372
+// (5000 x 2500, 75K edges), 459 and 407 (8000 x 5000, 60K), 835 and 593 (23117
+// x 9041, 301K), 2900 and 2181 (66000 x 13000, 2M: mean 68), 1188 and 1420
+// (30000 x 6000, 1M: mean 75), 5296 and 11000 (20000 x 20000, 4M, uniform),
+// 10176 and 5411 (80000 x 40000, 8M, uniform), 46266 and 12959 (the same,
+// power law), 15280 and 2046 (100003 x 50021, 2M).
+bool top_full_fits(const Job& J) {
+    const int64_t side = std::min(J.n_u, J.n_v);
+    const double m = (double)J.m;
+    return J.m >= 60000 && (side >= 32768 || (side >= 5000 && m * m <= 70.0 * 70.0 * J.n_u * (double)J.n_v));
+}
+
 // Top-vertex pipeline of a job whose sizes and options are set.
 void set_top(const bbc_ctx* ctx, Job& J, const bbc_options& o) {
     if (!top_fits(J)) return;
     J.top = true;
-    const bool fixed = o.band_words || o.wg_size;
-    const bool large = std::max(J.n_u, J.n_v) >= 16 * kTopWords;
+    const bool fixed = !J.pv && (o.band_words || o.wg_size);
+    const bool large = !J.pv && std::max(J.n_u, J.n_v) >= 16 * kTopWords;
     J.top_words = fixed ? wedge_band(o.band_words, o.wg_size, false) : large ? kTopWords : kTopSmallWords;
     J.top_wg = fixed ? wedge_block(o.band_words, o.wg_size, false) : large ? kTopWG : kTopSmallWG;
     J.top_grid = ctx->n_cu * (o.wg_per_cu > 0 ? o.wg_per_cu : top_blocks_per_cu(J.top_words, J.top_wg));
-    J.grid = J.top_grid;
     J.n_cu = ctx->n_cu;
     J.light_grid = ctx->n_cu * top_light_blocks_per_cu();
     J.light_w = std::min(J.light_w, kLightMaxWork);
@@ -973,7 +990,7 @@ void fill_stats(bbc_ctx* ctx, const Job& J, const DevStatus& h, int block) {
     S.bands = h.bands;
     S.n_blocks = J.n_blocks;
     S.dense_ops = J.dense_ops;
-    S.grid = J.grid;
+    S.grid = J.top ? J.top_grid : J.grid;
     S.block = block;
     S.band_words = J.top ? J.top_words : wedge_band(J.band_words, J.wg_size, J.pv != nullptr);
     S.tuned = J.tuned ? 1 : 0;
@@ -1263,9 +1280,9 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
         rc = block_job(ctx, opts, J, db, dt);
         if (rc != BBC_OK) return rc;
     }
-    if (!full && opts.n_blocks == 0) {
-        if (open) set_matrix(J, ctx->n_cu);
-        if (!J.mat) set_top(ctx, J, opts);
+    if (opts.n_blocks == 0) {
+        if (open && !full) set_matrix(J, ctx->n_cu);
+        if (!J.mat && (!full || (open && top_full_fits(J)))) set_top(ctx, J, opts);
     }
     if (fixed) {
         const auto fits = [&](size_t b) { return b <= kFixedScratchBytes && (ctx->limit <= 0 || b <= (size_t)ctx->limit); };

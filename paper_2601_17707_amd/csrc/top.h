@@ -93,6 +93,7 @@ struct TopArgs {
     DevStatus* st;
     TopCounts* tc;
     uint32_t* extra;         // anchors left to the bands by the hashed kernels
+    unsigned long long* pv;  // per-vertex counts in rank order (FULL kernels)
     int32_t n_u;
     int32_t statik, queue_chunk, light_chunk;
 };
@@ -107,6 +108,7 @@ struct TopBuild {
     TopBands* bands;
     uint32_t *ent, *cross, *mstart, *e, *idx;
     uint2* row;
+    unsigned long long* pv;
     TopCounts* tc;
 };
 
@@ -132,6 +134,9 @@ void top_work(const uint32_t* xkey, const uint32_t* vpay, const uint32_t* ent, c
 void top_schedule(const unsigned long long* work, const uint32_t* kx, int64_t n_u, int64_t n, uint32_t light_w,
                   uint32_t* skey, const DevStatus* st, hipStream_t s);
 void top_counts(const uint32_t* sorted, int64_t n, TopCounts* tc, hipStream_t s);
+// Per-vertex counts too, into out (id order); rank: of U ids, then of V ids.
+void launch_top_full(int n_cu, const TopArgs& a, const int32_t* rank, int64_t n, unsigned long long* out,
+                     hipStream_t s);
 void launch_top(int band_words, int wg, int grid, int light_grid, int n_cu, const TopArgs& a, hipStream_t s);
 int top_blocks_per_cu(int band_words, int wg);
 int top_light_blocks_per_cu();

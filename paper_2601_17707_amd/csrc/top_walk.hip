@@ -43,6 +43,7 @@ struct Flat {
 template <int GP>
 struct Group {
     uint32_t x[GP], tv[GP];
+    uint32_t sl[GP];  // slices (lanes) of the positions
     int32_t nv;
     bool full;
 };
@@ -105,7 +106,10 @@ __device__ __forceinline__ void flat_load(Flat& f, uint32_t* __restrict__ mark, 
     g.nv = f.total - j;
     g.full = j0 + GP * kWave <= f.total;
 #pragma unroll
-    for (int i = 0; i < GP; ++i) g.tv[i] = tab[(max(k[i], before) - 1u) & (kWave - 1)];
+    for (int i = 0; i < GP; ++i) {
+        g.sl[i] = (max(k[i], before) - 1u) & (kWave - 1);
+        g.tv[i] = tab[g.sl[i]];
+    }
     load_entries<GP>(ent, j, g);
 }
 
@@ -198,6 +202,94 @@ __device__ __forceinline__ uint32_t hash_group(uint32_t* __restrict__ tab, const
         pend &= next;
     }
     return acc;
+}
+
+// Per-vertex counts (FULL kernels).  A pair x, w with counters a and b holds
+// C(a,2) + C(b,2) butterflies of x and of w, and each of its wedges is in one
+// less than its counter's value of its middle's.  So once an anchor (or a band
+// of it) is counted, its wedges are read again, the counter of each is looked
+// up and what it gives its middle is summed per slice in LDS; then the
+// counters give the endpoints' shares.  All in rank order; k_top_credit moves
+// them to the ids.  Bound by the 64-bit atomics: on 2M power-law edges the
+// walk kernels take 1.62 ms (the total alone 0.6 ms), 0.43 ms of it the
+// endpoints' shares and 0.25 ms the second reading; the one-sided walk took
+// 14.6 ms.
+
+// The counters of key in the table (it is there).
+__device__ __forceinline__ uint32_t hash_look(const uint32_t* __restrict__ tab, uint32_t key, int lt) {
+    uint32_t h = (key * 0x9E3779B1u) >> (32 - lt);
+    for (;;) {
+        const uint32_t v = tab[h];
+        if ((v >> 12) == key) return v;
+        h = (h + 1u) & ((1u << lt) - 1u);
+    }
+}
+
+// Adds what a wave's positions give to the words of their slices: v[i] to
+// ys[at[i]], slices in order along the positions (GP per lane).  Neighbours
+// mostly share a slice, and 64 lanes adding to one LDS word are served one by
+// one, so the lanes that end in one slice are summed first.
+template <int GP>
+__device__ __forceinline__ void slice_add(uint32_t* __restrict__ ys, const uint32_t (&at)[GP], const uint32_t (&v)[GP]) {
+    uint32_t any = 0, tail = v[GP - 1];
+#pragma unroll
+    for (int i = 0; i < GP; ++i) any |= v[i];
+    if (!__any(any != 0u)) return;
+    const uint32_t own = at[GP - 1];
+#pragma unroll
+    for (int i = 0; i < GP - 1; ++i) {
+        if (at[i] == own) tail += v[i];
+        else if (v[i]) atomicAdd(&ys[at[i]], v[i]);
+    }
+    const int lane = lane_id();
+    const uint32_t sum = wave_inclusive_sum_dpp(tail);
+    const uint32_t prev = (uint32_t)__shfl_up((int)own, 1, kWave);
+    const unsigned long long heads = __ballot(lane == 0 || prev != own);
+    const int h = 63 - __clzll(heads & (~0ull >> (63 - lane)));  // first lane of this lane's run
+    const uint32_t before = (uint32_t)__shfl((int)sum, h > 0 ? h - 1 : 0, kWave);
+    const bool last = lane == kWave - 1 || ((heads >> (lane + 1)) & 1ull);
+    const uint32_t run = sum - (h > 0 ? before : 0u);
+    if (last && run) atomicAdd(&ys[own], run);
+}
+
+// Second reading of one chunk's slices: what its wedges give the middles, per
+// slice in ys (one word per lane, zero before and after), added to pv at y
+// (this lane's middle).  At most 62 per wedge and 2^14 wedges.
+template <int GP>
+__device__ __forceinline__ void hash_credit(Flat f, uint32_t* __restrict__ mark, const uint32_t* __restrict__ stab,
+                                            const uint32_t* __restrict__ ent, const uint32_t* __restrict__ tab, uint32_t rx,
+                                            int lt, uint32_t* __restrict__ ys, unsigned long long* __restrict__ pv,
+                                            uint32_t y) {
+    const int lane = lane_id();
+    f.carry = 0;
+    for (int32_t j0 = 0; j0 < f.total; j0 += GP * kWave) {
+        Group<GP> g;
+        flat_load<GP>(f, mark, stab, ent, j0, g);
+        uint32_t give[GP];
+#pragma unroll
+        for (int i = 0; i < GP; ++i) {
+            give[i] = 0;
+            if (i >= g.nv) continue;
+            const uint32_t v = hash_look(tab, (rx - g.x[i]) & ((1u << kLightKeyBits) - 1u), lt);
+            give[i] = ((v >> (((g.x[i] ^ g.tv[i]) >> 31) * 6u)) & 63u) - 1u;
+        }
+        slice_add<GP>(ys, g.sl, give);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t v = ys[lane];
+    if (v) {
+        atomicAdd(&pv[y], (unsigned long long)v);
+        ys[lane] = 0;
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Endpoints' shares of slot v of a table (anchor rank rx, first vertex of its
+// side xb).
+__device__ __forceinline__ void hash_share(uint32_t v, uint32_t rx, uint32_t xb, unsigned long long* __restrict__ pv) {
+    const uint32_t a = v & 63u, b = (v >> 6) & 63u;
+    const uint32_t s = a * (a - (a > 0u)) + b * (b - (b > 0u));
+    if (s) atomicAdd(&pv[xb + rx - (v >> 12)], (unsigned long long)(s >> 1));
 }
 
 // A middle as read ahead: entry, end of its wedges, start of its list.
@@ -390,6 +482,7 @@ typedef uint16_t __attribute__((may_alias)) mark16;
 struct TopTask {
     uint32_t a0, k, r, lo, hi, words;
     int32_t b, mode;
+    uint32_t x;  // the anchor
     uint32_t flags;  // bit 0: the band is the side's first; bit 1: the anchor lies in it; bit 2: fine chunks
 };
 
@@ -397,13 +490,14 @@ struct TopTask {
 __device__ __forceinline__ TopTask uniform_task(const TopTask& s) {
     auto u = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
     return TopTask{u(s.a0),         u(s.k),           u(s.r),          u(s.lo),        u(s.hi), u(s.words),
-                   (int32_t)u((uint32_t)s.b), (int32_t)u((uint32_t)s.mode), u(s.flags)};
+                   (int32_t)u((uint32_t)s.b), (int32_t)u((uint32_t)s.mode), u(s.x), u(s.flags)};
 }
 
-template <int WG, int BW>
+template <int WG, int BW, bool FULL>
 struct BandShared {
     alignas(16) uint32_t cnt[BW];
     QuadLds flat[WG / kWave];
+    uint32_t ys[FULL ? WG / kWave : 1][FULL ? kLaneMids * kWave : 1];  // per slice: what its wedges give the middle
     unsigned long long red[WG / kWave];
     TopTask task[2];
     uint32_t next;  // next chunk of middles
@@ -462,7 +556,8 @@ __device__ __forceinline__ void quad_begin(QuadFlat& f, QuadLds& sh, const Quad&
 
 // Slice words of the group at position j0 (groups in order) of a chunk with
 // wedges, several slices per lane (16-bit marks); see flat_load.
-__device__ __forceinline__ void quad_words(QuadFlat& f, QuadLds& sh, int32_t j0, uint32_t (&tv)[kQuadGP]) {
+__device__ __forceinline__ void quad_words(QuadFlat& f, QuadLds& sh, int32_t j0, uint32_t (&tv)[kQuadGP],
+                                           uint32_t (&at)[kQuadGP]) {
     constexpr int GP = kQuadGP;
     const int lane = lane_id();
     // marks hold the byte offset of the slice's word, plus 4
@@ -491,8 +586,10 @@ __device__ __forceinline__ void quad_words(QuadFlat& f, QuadLds& sh, int32_t j0,
     f.carry = max(f.carry, (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1));
     // every k is at least 4: position 0 is marked
 #pragma unroll
-    for (int i = 0; i < GP; ++i)
-        tv[i] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(sh.tab) + (max(k[i], before) - 4u));
+    for (int i = 0; i < GP; ++i) {
+        at[i] = max(k[i], before) - 4u;  // byte offset of the slice's word
+        tv[i] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(sh.tab) + at[i]);
+    }
 }
 
 // Counts the task's wedges (all waves).  cur holds the wave's first chunk,
@@ -505,9 +602,9 @@ __device__ __forceinline__ void quad_words(QuadFlat& f, QuadLds& sh, int32_t j0,
 // step keeps the loop inside the registers and the instruction cache (two
 // groups by turns, with every step twice and another copy for 32-bit counters,
 // spilled and took 9.95 ms instead of 6.7 ms on the 20M-edge power-law graph).
-template <int WG, int BW>
-__device__ __forceinline__ unsigned long long band_walk(BandShared<WG, BW>& sh, const TopArgs& a, const TopTask& t,
-                                                        Quad& cur) {
+template <int WG, int BW, bool FULL>
+__device__ __forceinline__ unsigned long long band_walk(BandShared<WG, BW, FULL>& sh, const TopArgs& a,
+                                                        const TopTask& t, Quad& cur) {
     constexpr int GP = kQuadGP;
     const int lane = lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -556,8 +653,8 @@ __device__ __forceinline__ unsigned long long band_walk(BandShared<WG, BW>& sh, 
             if (lane == 0) acc -= (unsigned long long)f.total;
         }
         const bool more = f.total > 0;
-        uint32_t tn[GP];
-        if (more) quad_words(f, fl, j0, tn);
+        uint32_t tn[GP], at[GP];
+        if (more) quad_words(f, fl, j0, tn, at);
         __builtin_amdgcn_sched_barrier(0);
         uint32_t byte[GP], inc[GP];
 #pragma unroll
@@ -611,7 +708,133 @@ __device__ __forceinline__ unsigned long long band_walk(BandShared<WG, BW>& sh, 
     return acc;
 }
 
+// The second reading of a counted band's wedges (FULL): chunks are dealt as in
+// band_walk; the middles' shares are summed per slice, 32 bits wide (a band of
+// 32-bit counters, whose sums may need more, adds each share at once; its ys
+// hold the slices' middles).
 template <int WG, int BW>
+__device__ __forceinline__ void band_credit(BandShared<WG, BW, true>& sh, const TopArgs& a, const TopTask& t) {
+    constexpr int GP = kQuadGP;
+    const int lane = lane_id();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    QuadLds& fl = sh.flat[wave];
+    uint32_t* const ys = sh.ys[wave];
+    const BandFields bf = band_fields(t.mode, t.words);
+    const bool wide = t.mode == 3;
+    const uint32_t ones = wide ? ~0u : (1u << (4 << t.mode)) - 1u;
+    const ChunkLayout l = chunk_layout(t.flags & 4u);
+    const uint32_t n_ch = quad_chunks(l, t.k);
+    const uint32_t yb = t.x < (uint32_t)a.n_u ? (uint32_t)a.n_u : 0u;
+    const char* const ent = reinterpret_cast<const char*>(a.ent);
+    const char* const cnt = reinterpret_cast<const char*>(sh.cnt);
+    uint32_t c = WG / kWave - 1u - wave;
+    Quad q;
+    quad_load(q, a, t.a0, t.k, n_ch, c, l);
+    while (c < n_ch) {
+        quad_bounds(q, a, t.b);
+        QuadFlat f;
+        quad_begin(f, fl, q, a, t, c >= l.c3);
+        uint32_t y[kLaneMids];
+#pragma unroll
+        for (int j = 0; j < kLaneMids; ++j) {
+            y[j] = yb + top_rank(q.e[j]);
+            if (wide) ys[kLaneMids * lane + j] = y[j];
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t next = 0;
+        if (lane == 0) next = atomicAdd(&sh.next, 1u);
+        c = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
+        quad_load(q, a, t.a0, t.k, n_ch, c, l);  // ahead
+        for (int32_t j0 = 0; j0 < f.total; j0 += GP * kWave) {
+            uint32_t tv[GP], at[GP], x[GP];
+            quad_words(f, fl, j0, tv, at);
+            const int32_t j = j0 + lane * GP, nv = f.total - j;
+#pragma unroll
+            for (int i = 0; i < GP; ++i)
+                x[i] = *reinterpret_cast<const uint32_t*>(ent + (i < nv ? (tv[i] + (uint32_t)(j + i)) << 2 : 0u));
+            uint32_t give[GP];
+#pragma unroll
+            for (int i = 0; i < GP; ++i) {
+                at[i] >>= 2;
+                give[i] = 0;
+                if (i >= nv) continue;
+                const uint32_t p = mul_u24(x[i], bf.mul), ty = x[i] ^ tv[i];
+                const uint32_t word = (p & bf.wmask) | (wide ? ty >> 31 << 2 : 0u);
+                const uint32_t sh_ = wide ? 0u : (((p & bf.fm) << 3) | ((ty >> bf.ts) & bf.tm)) & 31u;
+                const uint32_t v = (*reinterpret_cast<const uint32_t*>(cnt + word) >> sh_) & ones;
+                if (!wide) give[i] = v - 1u;
+                else if (v > 1u) atomicAdd(&a.pv[ys[at[i]]], (unsigned long long)(v - 1u));
+            }
+            slice_add<GP>(ys, at, give);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < kLaneMids; ++j) {
+            const uint32_t v = ys[kLaneMids * lane + j];
+            if (v) {
+                if (!wide) atomicAdd(&a.pv[y[j]], (unsigned long long)v);
+                ys[kLaneMids * lane + j] = 0;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Endpoints' shares of a counted band, which is cleared; returns this thread's
+// sum.  Slot s of the band holds the rank r in it with r kSlotMul = s modulo
+// the band's slots.
+template <int WG>
+__device__ __forceinline__ unsigned long long share_words(uint32_t* __restrict__ cnt, const TopArgs& a,
+                                                          const TopTask& t) {
+    unsigned long long sum = 0;
+    const uint32_t xb = t.x < (uint32_t)a.n_u ? 0u : (uint32_t)a.n_u;
+    auto give = [&](uint32_t slot, uint32_t slots, unsigned long long ca, unsigned long long cb) {
+        const unsigned long long s = (ca * (ca - (ca > 0)) + cb * (cb - (cb > 0))) / 2ull;
+        if (!s) return;
+        const uint32_t r = t.lo + ((slot * kSlotInv - t.lo) & (slots - 1u));
+        atomicAdd(&a.pv[xb + r], s);
+        sum += s;
+    };
+    if (t.mode == 3) {
+        uint2* p = reinterpret_cast<uint2*>(cnt);
+        for (uint32_t i = threadIdx.x; i < t.words / 2u; i += WG) {
+            const uint2 v = p[i];
+            if (v.x | v.y) {
+                p[i] = uint2{0u, 0u};
+                give(i, t.words / 2u, v.x, v.y);
+            }
+        }
+        return sum;
+    }
+    // a and b of an endpoint sum to at most 65535 here: 32 bits hold the shares
+    const uint32_t per = 4u >> t.mode, bits = 4u << t.mode, ones = (1u << bits) - 1u;  // slots per word, counter bits
+    const uint32_t slots = t.words * per;
+    const uint32_t pairs = t.mode == 0 ? 0xeeeeeeeeu : t.mode == 1 ? 0xfefefefeu : 0xfffefffeu;  // a counter of 2 or more
+    auto word = [&](uint32_t i, uint32_t v) {
+        if (!(v & pairs)) return;
+        for (uint32_t k = 0; k < per; ++k, v = bits == 16u ? 0u : v >> (2u * bits)) {
+            const uint32_t ca = v & ones, cb = (v >> bits) & ones;
+            const uint32_t s = (ca * (ca - (ca > 0u)) >> 1) + (cb * (cb - (cb > 0u)) >> 1);
+            if (!s) continue;
+            const uint32_t r = t.lo + (((i * per + k) * kSlotInv - t.lo) & (slots - 1u));
+            atomicAdd(&a.pv[xb + r], (unsigned long long)s);
+            sum += s;
+        }
+    };
+    for (uint32_t w4 = threadIdx.x; w4 < t.words / 4u; w4 += WG) {
+        uint4* p = reinterpret_cast<uint4*>(&cnt[w4 * 4u]);
+        const uint4 v = *p;
+        if (!(v.x | v.y | v.z | v.w)) continue;
+        *p = uint4{0u, 0u, 0u, 0u};
+        word(w4 * 4u, v.x);
+        word(w4 * 4u + 1u, v.y);
+        word(w4 * 4u + 2u, v.z);
+        word(w4 * 4u + 3u, v.w);
+    }
+    return sum;
+}
+
+template <int WG, int BW, bool FULL>
 __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
     if (*(volatile const int32_t*)&a.st->flags) return;  // input error: nothing to count
     const uint32_t n_split = *(volatile const uint32_t*)&a.tc->n_tier[0];
@@ -619,11 +842,13 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
     const uint32_t nb_max = *(volatile const uint32_t*)&a.tc->nb_max;
     const unsigned long long n_tasks = (unsigned long long)n_all * nb_max;
     if (blockIdx.x >= n_tasks) return;  // the first task is the workgroup's own: idle ones touch no queue
-    __shared__ BandShared<WG, BW> sh;
+    __shared__ BandShared<WG, BW, FULL> sh;
     const int tid = threadIdx.x, lane = lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     for (int i = tid; i < BW; i += WG) sh.cnt[i] = 0;
     reinterpret_cast<uint2*>(sh.flat[wave].mark)[lane] = uint2{0u, 0u};
+    if constexpr (FULL)
+        for (int j = lane; j < kLaneMids * kWave; j += kWave) sh.ys[wave][j] = 0;
     // Thread 0 takes the next task that has a band (widest counters, which
     // hold most wedges, first), each pop sent out one task ahead; k = 0 marks
     // the end.
@@ -641,7 +866,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
             if (b >= x.nbx) continue;
             const TopRange rg = make_range(x.B, b, b + 1, x.nbx, x.r);
             t = TopTask{x.a0,  x.k, (uint32_t)x.r,         rg.lo, rg.hi, 1u << x.B.lw,
-                        b,     band_mode(x.B, b), (rg.first ? 1u : 0u) | (rg.last ? 2u : 0u) | (a.work[id] >= kFineWork ? 4u : 0u)};
+                        b,     band_mode(x.B, b), id, (rg.first ? 1u : 0u) | (rg.last ? 2u : 0u) | (a.work[id] >= kFineWork ? 4u : 0u)};
             return;
         }
     };
@@ -669,10 +894,21 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
         if (tid == 0) take(sh.task[it ^ 1u]);
         unsigned long long mine = band_walk(sh, a, t, cur);
         __syncthreads();
+        if constexpr (FULL) {
+            if (tid == 0) sh.next = WG / kWave;
+            __syncthreads();
+            band_credit(sh, a, t);
+            __syncthreads();
+        }
         const TopTask n = uniform_task(sh.task[it ^ 1u]);
         if (n.k > 0) first_chunk(n);
         if (tid == 0) sh.next = WG / kWave;
-        if (t.mode == 0) mine += reduce_words<0, WG>(sh.cnt, t.words);
+        if constexpr (FULL) {
+            const unsigned long long s = share_words<WG>(sh.cnt, a, t);
+            const unsigned long long w = wave_sum(s);
+            if (lane == 0 && w) atomicAdd(&a.pv[t.x], w);
+            mine = 2ull * s;
+        } else if (t.mode == 0) mine += reduce_words<0, WG>(sh.cnt, t.words);
         else if (t.mode == 1) mine += reduce_words<1, WG>(sh.cnt, t.words);
         else if (t.mode == 2) mine += reduce_words<2, WG>(sh.cnt, t.words);
         else mine += reduce_words<3, WG>(sh.cnt, t.words);
@@ -693,16 +929,17 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
 // go to the waves in turn; the next anchor is read while this one's table is
 // cleared.  An anchor with a counter past 63 is left to the bands (kernel
 // k_top_bands runs after this one).
-template <int WG, int LTMAX>
+template <int WG, int LTMAX, bool FULL>
 struct HashShared {
     alignas(16) uint32_t tab[1 << LTMAX];
     FlatLds<4> flat[WG / kWave];
     unsigned long long red[WG / kWave];
     TopTask task[2];
-    uint32_t full;
+    uint32_t full, any;
+    uint32_t ys[FULL ? WG / kWave : 1][FULL ? kWave : 1];
 };
 
-template <int WG, int LTMAX, int CH0, int CH>
+template <int WG, int LTMAX, int CH0, int CH, bool FULL>
 __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
     if (*(volatile const int32_t*)&a.st->flags) return;
     constexpr int NW = WG / kWave, GP = 4;
@@ -710,7 +947,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
     const uint32_t p1 = *(volatile const uint32_t*)&a.tc->n_tier[tier + 1];
     const uint32_t n_tasks = (p1 - p0 + (uint32_t)a.queue_chunk - 1u) / (uint32_t)a.queue_chunk;
     if (blockIdx.x >= n_tasks) return;  // the first task is the workgroup's own: idle ones touch no queue
-    __shared__ HashShared<WG, LTMAX> sh;
+    __shared__ HashShared<WG, LTMAX, FULL> sh;
     const int tid = threadIdx.x, lane = lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     FlatLds<GP>& fl = sh.flat[wave];
@@ -743,9 +980,10 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
         t.k = a.kx[x];
     };
     if (tid == 0) {
-        sh.full = 0;
+        sh.full = sh.any = 0;
         take(sh.task[0]);
     }
+    if constexpr (FULL) sh.ys[wave][lane] = 0;
     // chunk c's middles from the highest down: CH0 each in the first NW chunks
     // (the longest lists), CH in the others; the other lanes read the
     // anchor's first entry and hold nothing
@@ -796,8 +1034,30 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
             }
         }
         if (full) sh.full = 1u;
+        if (FULL && s) sh.any = 1u;
         __syncthreads();
         const bool bad = sh.full != 0;
+        if constexpr (FULL) {
+            if (!bad && sh.any) {  // the same for every thread
+                const uint32_t yb = t.lo < (uint32_t)a.n_u ? (uint32_t)a.n_u : 0u;
+                for (uint32_t c = w0; c < n_ch; c += NW) {
+                    mids(t, c, m, has);
+                    Flat f;
+                    flat_begin(f, fl.tab, m.ms, has ? (int32_t)(m.cr - m.ms) : 0, m.e);
+                    hash_credit<GP>(f, fl.mark, fl.tab, a.ent, sh.tab, t.r, t.mode, sh.ys[wave], a.pv,
+                                    yb + top_rank(m.e));
+                }
+                const unsigned long long w = wave_sum((unsigned long long)s);
+                if (lane == 0 && w) atomicAdd(&a.pv[t.lo], w);
+                __syncthreads();
+                if (tid == 0) sh.any = 0;
+                for (int i = tid; i < (1 << t.mode); i += WG) {
+                    const uint32_t v = sh.tab[i];
+                    if (v) hash_share(v, t.r, (uint32_t)a.n_u - yb, a.pv);
+                }
+                __syncthreads();
+            }
+        }
         const TopTask n = uniform_task(sh.task[it ^ 1u]);
         if (n.k > 0) mids(n, w0, m, has);
         unsigned long long mine = bad ? 0ull : 2ull * s;
@@ -829,6 +1089,7 @@ struct LightHead {
     uint32_t x, a0, k;
 };
 
+template <bool FULL>
 __global__ __launch_bounds__(kTopLightWG, 4) void k_top_light(TopArgs a) {
     if (*(volatile const int32_t*)&a.st->flags) return;
     constexpr int NW = kTopLightWG / kWave, TW = 1 << kTopLightLT, GP = kLightGP;
@@ -846,6 +1107,8 @@ __global__ __launch_bounds__(kTopLightWG, 4) void k_top_light(TopArgs a) {
     };
     clear(TW);
     mark[lane] = 0u;
+    __shared__ uint32_t ys[FULL ? NW : 1][FULL ? kWave : 1];
+    if constexpr (FULL) ys[wave][lane] = 0u;
     __builtin_amdgcn_wave_barrier();
     const uint32_t n_heavy = *(volatile const uint32_t*)&a.tc->n_tier[kTopTiers];
     const uint32_t n_walk = *(volatile const uint32_t*)&a.tc->n_walk;
@@ -902,6 +1165,7 @@ __global__ __launch_bounds__(kTopLightWG, 4) void k_top_light(TopArgs a) {
             begin(1 - b);
             const uint32_t x = h[b].x;
             const uint32_t rx = x >= (uint32_t)a.n_u ? x - (uint32_t)a.n_u : x;
+            const LightHead own = h[b];
             lanes(h2, m);
             h[b] = h2;
             head(x3, h2);
@@ -915,6 +1179,21 @@ __global__ __launch_bounds__(kTopLightWG, 4) void k_top_light(TopArgs a) {
             for (int32_t j0 = GP * kWave; j0 < f[b].total; j0 += GP * kWave) {
                 flat_load<GP>(f[b], mark, flat[wave][b].tab, a.ent, j0, gr[b]);
                 s += hash_group<GP, false>(tab, gr[b], rx, lt, full);
+            }
+            if constexpr (FULL) {
+                if (__any(s != 0u)) {
+                    const uint32_t yb = x < (uint32_t)a.n_u ? (uint32_t)a.n_u : 0u;
+                    const uint32_t e = a.ent[own.a0 + ((uint32_t)lane < own.k ? (uint32_t)lane : 0u)];
+                    hash_credit<GP>(f[b], mark, flat[wave][b].tab, a.ent, tab, rx, lt, ys[wave], a.pv,
+                                    yb + top_rank(e));
+                    const unsigned long long w = wave_sum((unsigned long long)s);
+                    if (lane == 0) atomicAdd(&a.pv[x], w);
+                    for (int i = lane; i < (1 << lt); i += kWave) {
+                        const uint32_t v = tab[i];
+                        if (v) hash_share(v, rx, (uint32_t)a.n_u - yb, a.pv);
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
             }
             clear(1 << lt);
             acc += 2u * s;
@@ -932,13 +1211,13 @@ __global__ __launch_bounds__(kTopLightWG, 4) void k_top_light(TopArgs a) {
 template <int WG, int BW>
 static int top_occ() {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_top_bands<WG, BW>, WG, 0) != hipSuccess) return 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_top_bands<WG, BW, false>, WG, 0) != hipSuccess) return 1;
     return n > 0 ? n : 1;
 }
 
 template <int WG, int BW>
 static void top_launch(const TopArgs& a, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((k_top_bands<WG, BW>), dim3(grid), dim3(WG), 0, s, a);
+    hipLaunchKernelGGL((k_top_bands<WG, BW, false>), dim3(grid), dim3(WG), 0, s, a);
 }
 
 struct TopShape {
@@ -960,26 +1239,45 @@ static const TopShape& top_shape(int band_words, int wg) {
 
 int top_blocks_per_cu(int band_words, int wg) { return top_shape(band_words, wg).occ(); }
 
-int top_light_blocks_per_cu() {
+template <class K>
+static int kernel_occ(K* kernel, int wg) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_top_light, kTopLightWG, 0) != hipSuccess) return 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, wg, 0) != hipSuccess) return 1;
     return n > 0 ? n : 1;
 }
 
-template <int WG, int LT, int CH0, int CH>
-static int hash_occ() {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (k_top_hash<WG, LT, CH0, CH>), WG, 0) != hipSuccess) return 1;
-    return n > 0 ? n : 1;
+int top_light_blocks_per_cu() { return kernel_occ(k_top_light<false>, kTopLightWG); }
+
+// Per-vertex output in id order from the counts in rank order.
+__global__ void k_top_credit(const unsigned long long* __restrict__ pv, const int32_t* __restrict__ rank, int64_t n_u,
+                             int64_t n, unsigned long long* __restrict__ out) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = pv[(i < n_u ? 0 : n_u) + rank[i]];
+}
+
+void launch_top_full(int n_cu, const TopArgs& a, const int32_t* rank, int64_t n, unsigned long long* out,
+                     hipStream_t s) {
+    constexpr int WG = 512, BW = 16384;
+    static const int occ0 = kernel_occ(k_top_hash<1024, 15, 4, 16, true>, 1024),
+                     occ1 = kernel_occ(k_top_hash<256, 13, 8, 32, true>, 256),
+                     occ2 = kernel_occ(k_top_light<true>, kTopLightWG), occ3 = kernel_occ(k_top_bands<WG, BW, true>, WG);
+    hipLaunchKernelGGL((k_top_hash<1024, 15, 4, 16, true>), dim3(n_cu * occ0), dim3(1024), 0, s, a, 0);
+    hipLaunchKernelGGL((k_top_hash<256, 13, 8, 32, true>), dim3(n_cu * occ1), dim3(256), 0, s, a, 1);
+    hipLaunchKernelGGL(k_top_light<true>, dim3(n_cu * occ2), dim3(kTopLightWG), 0, s, a);
+    hipLaunchKernelGGL((k_top_bands<WG, BW, true>), dim3(n_cu * occ3), dim3(WG), 0, s, a);
+    const int64_t g = (n + 255) / 256;
+    hipLaunchKernelGGL(k_top_credit, dim3((unsigned)(g > 4096 ? 4096 : g)), dim3(256), 0, s, a.pv, rank, (int64_t)a.n_u, n,
+                       out);
 }
 
 // The tiers' kernels: tables of twice the tier's largest work.
 void launch_top(int band_words, int wg, int grid, int light_grid, int n_cu, const TopArgs& a, hipStream_t s) {
     static_assert(kTierWork[0] * 2 == 1u << 15 && kTierWork[1] * 2 == 1u << 13, "table sizes");
-    static const int occ0 = hash_occ<1024, 15, 4, 16>(), occ1 = hash_occ<256, 13, 8, 32>();
-    hipLaunchKernelGGL((k_top_hash<1024, 15, 4, 16>), dim3(n_cu * occ0), dim3(1024), 0, s, a, 0);
-    hipLaunchKernelGGL((k_top_hash<256, 13, 8, 32>), dim3(n_cu * occ1), dim3(256), 0, s, a, 1);
-    hipLaunchKernelGGL(k_top_light, dim3(light_grid), dim3(kTopLightWG), 0, s, a);
+    static const int occ0 = kernel_occ(k_top_hash<1024, 15, 4, 16, false>, 1024),
+                     occ1 = kernel_occ(k_top_hash<256, 13, 8, 32, false>, 256);
+    hipLaunchKernelGGL((k_top_hash<1024, 15, 4, 16, false>), dim3(n_cu * occ0), dim3(1024), 0, s, a, 0);
+    hipLaunchKernelGGL((k_top_hash<256, 13, 8, 32, false>), dim3(n_cu * occ1), dim3(256), 0, s, a, 1);
+    hipLaunchKernelGGL(k_top_light<false>, dim3(light_grid), dim3(kTopLightWG), 0, s, a);
     top_shape(band_words, wg).launch(a, grid, s);
 }
 

@@ -2,7 +2,7 @@
 kernels' regimes meet (waves, the two hashed tables, counter bands), counters
 that overflow a hashed slot, every counter width of the bands, band widths
 below and above a side, unindexed lists, the largest side ratio, and batches,
-all against the oracle (whole numbers: equality)."""
+and the per-vertex counts of the same walk, all against the oracle (whole numbers: equality)."""
 import numpy as np
 import pytest
 
@@ -132,3 +132,47 @@ def test_limits_fall_back(ctx):
         except bbc.BbcError as e:
             assert e.status == bbc.ENOMEM and ok == 0
     assert ok >= 3
+
+
+def pv_check(ctx, g):
+    import torch
+
+    pv = torch.empty(g.n_u + g.n_v, dtype=torch.int64, device="cuda:0")
+    t = ctx.count(*bbc.graph_tensors(g, "cuda:0"), g.n_v, per_vertex=pv)
+    assert t == oracle.count(g)
+    assert np.array_equal(pv.cpu().numpy().astype(np.uint64), np.asarray(oracle.per_vertex(g)).astype(np.uint64))
+
+
+def padded(g, m=70_000):
+    """The graph beside a sparse one, so that the call has at least m edges
+    (smaller per-vertex calls take the one-sided walk)."""
+    h = synth.uniform_graph(9000, 8000, m, 0.3, 3)
+    u = np.concatenate([np.repeat(np.arange(x.n_u), np.diff(x.offsets)) + o for x, o in ((g, 0), (h, g.n_u))])
+    v = np.concatenate([x.adj.astype(np.int64) + o for x, o in ((g, 0), (h, g.n_v))])
+    return synth.from_edges(g.n_u + h.n_u, g.n_v + h.n_v, u, v, np.concatenate([g.signs, h.signs]))
+
+
+@pytest.mark.parametrize("n_mid,n_end", [(2, 1), (63, 16), (64, 16), (64, 63), (65, 64), (129, 128), (600, 40)])
+def test_per_vertex_regimes(ctx, n_mid, n_end):
+    pv_check(ctx, padded(star_pairs(n_mid, n_end, n_mid * 1000 + n_end)))
+
+
+@pytest.mark.parametrize("mids,dense", [(70, 60), (300, 12), (40, 3000), (700, 400), (70_000, 3)])
+def test_per_vertex_widths(ctx, mids, dense):
+    """Complete blocks of the counter widths: pairs with up to 70,000 common
+    middles, more than a hashed slot or a 16-bit counter holds."""
+    rng = np.random.default_rng(mids)
+    u, v = np.meshgrid(np.arange(dense), np.arange(mids), indexing="ij")
+    keep = rng.random(u.size) < 0.95 if mids < 10_000 else np.ones(u.size, bool)
+    sg = np.where(rng.random(u.size) < 0.3, -1, 1)
+    pv_check(ctx, padded(synth.from_edges(dense, mids, u.ravel()[keep], v.ravel()[keep], sg[keep])))
+
+
+@pytest.mark.parametrize("n_u,n_v,m", [(40_000, 30_000, 400_000), (5_000, 40_000, 300_000), (40_000, 5_000, 300_000)])
+def test_per_vertex_power_law(ctx, n_u, n_v, m):
+    pv_check(ctx, synth.chung_lu_graph(n_u, n_v, m, 2.1, 2.1, n_u / 10, n_v / 10, 11, p_neg=0.4))
+
+
+@pytest.mark.parametrize("n,m", [(5000, 59_999), (5000, 60_000), (4999, 60_000), (5000, 350_000), (5000, 350_001)])
+def test_per_vertex_rule_edges(ctx, n, m):
+    pv_check(ctx, synth.uniform_graph(n, n + 1 if m < 350_000 else n, m, 0.3, m))
