@@ -443,13 +443,16 @@ __global__ void k_check_dup(const uint32_t* ckey, const uint32_t* packed, int64_
 // thread per anchor-list entry; the entries of an anchor are contiguous, so
 // a wave sums runs of equal rank with a segmented scan and adds each run
 // once.  st->wedges receives the sum over centres of C(deg, 2), st->walked
-// the wedges the walk visits.
+// the wedges the walk visits.  Bound by the latency of the random reads per
+// entry: 20M edges of 2.5M x 100K vertices take 360 us with two entries a
+// thread and as many workgroups as that gives, 387 us with four on 4096.
+constexpr int kWorkItems = 2;  // entries per thread whose loads are in flight together
 __global__ __launch_bounds__(256) void k_work(const uint32_t* __restrict__ apack, const int32_t* __restrict__ acent,
                                               const int32_t* __restrict__ back, const uint32_t* __restrict__ coff,
                                               int64_t m, unsigned long long* __restrict__ work, DevStatus* st,
                                               HybridView hv) {
     if (input_bad(st)) return;
-    constexpr int U = 4;  // entries per thread whose loads are in flight together
+    constexpr int U = kWorkItems;
     __shared__ unsigned long long red[256 / kWave];
     const int lane = lane_id();
     unsigned long long all = 0, walked = 0;
@@ -728,7 +731,7 @@ void launch_work(const uint32_t* apack, const int32_t* acent, const int32_t* bac
     if (n_s <= 0) return;
     fill_bytes(work, n_s * 8, s);
     if (m > 0)
-        hipLaunchKernelGGL(k_work, dim3(grid_for(m, 256, 4096)), dim3(256), 0, s, apack, acent, back, coff, m, work,
+        hipLaunchKernelGGL(k_work, dim3(grid_for(m, 256 * kWorkItems, 65536)), dim3(256), 0, s, apack, acent, back, coff, m, work,
                            st, hv);
     hipLaunchKernelGGL(k_work_keys, dim3(grid_for(n_s, 256)), dim3(256), 0, s, work, n_s, key, aoff, agraph,
                        rank_end, hv.ablk1, light_w, st);

@@ -238,7 +238,10 @@ __global__ void k_top_rows(const uint32_t* __restrict__ off, const uint32_t* __r
 // sums over the lanes and one atomic per vertex and wave.  Bound by the random
 // read per middle (20M power-law edges: one 8-byte row instead of three words
 // from two arrays, and the index filled on the way instead of by a kernel of
-// its own that read the entries again: 619 us instead of 558 + 270 us).
+// its own that read the entries again: 619 us instead of 558 + 270 us).  Many
+// workgroups of two entries a thread hide its latency better than 2048 of four
+// in a loop: 492 and 627 us there, 437 and 609 us on 20M uniform edges.
+constexpr int kTopWorkItems = 2;  // entries per thread whose loads are in flight together
 __global__ __launch_bounds__(256) void k_top_work(const uint32_t* __restrict__ xkey, const uint32_t* __restrict__ vpay,
                                                   const uint32_t* __restrict__ ent, const uint32_t* __restrict__ cross,
                                                   const uint2* __restrict__ row, const uint32_t* __restrict__ thr,
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(256) void k_top_work(const uint32_t* __restrict__ x
                                                   uint32_t* __restrict__ mbase, uint32_t* __restrict__ kx,
                                                   unsigned long long* __restrict__ work, const DevStatus* st) {
     if (top_bad(st)) return;
-    constexpr int U = 4;  // entries per thread whose loads are in flight together
+    constexpr int U = kTopWorkItems;
     constexpr uint32_t kNone = 0xffffffffu;
     const int lane = lane_id();
     const TopBands BU = bands[0], BV = bands[1];
@@ -411,7 +414,7 @@ void top_index(const uint32_t* off, int64_t n_u, int64_t n, const TopBands* band
 void top_work(const uint32_t* xkey, const uint32_t* vpay, const uint32_t* ent, const uint32_t* cross, const uint2* row,
               const uint32_t* thr, const TopBands* bands, int64_t m, int32_t n_u, uint32_t* idx, uint32_t* mstart,
               uint32_t* mbase, uint32_t* kx, unsigned long long* work, const DevStatus* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_top_work, dim3(top_grid(2 * m, 1024, 2048)), dim3(256), 0, s, xkey, vpay, ent, cross, row, thr,
+    hipLaunchKernelGGL(k_top_work, dim3(top_grid(2 * m, 256 * kTopWorkItems)), dim3(256), 0, s, xkey, vpay, ent, cross, row, thr,
                        bands, m, n_u, idx, mstart, mbase, kx, work, st);
 }
 
