@@ -383,25 +383,37 @@ __device__ __forceinline__ unsigned long long choose2_u64(long long d) {
     return d > 1 ? (unsigned long long)d * (unsigned long long)(d - 1) / 2ull : 0ull;
 }
 
-__global__ void k_side_rows(const int32_t* off, int32_t n_u, unsigned long long* out) {
+// The sums leave one atomic per workgroup of a small grid, and the V degrees
+// are counted in nrep replicas (workgroup b into replica b % nrep): atomics on
+// one address are served about 18 ns apart.
+constexpr int kSideGrid = 512;
+__global__ __launch_bounds__(256) void k_side_rows(const int32_t* off, int32_t n_u, unsigned long long* out) {
+    __shared__ unsigned long long red[256 / kWave];
     unsigned long long acc = 0;
     GRID_STRIDE(i, n_u) acc += choose2_u64((long long)off[i + 1] - (long long)off[i]);
-    acc = wave_sum(acc);
-    if (lane_id() == 0 && acc) atomicAdd(&out[0], acc);
+    acc = block_sum<256>(acc, red);
+    if (threadIdx.x == 0 && acc) atomicAdd(&out[0], acc);
 }
 
-__global__ void k_side_hist(const int32_t* adj, int64_t m, int32_t n_v, uint32_t* deg) {
+__global__ void k_side_hist(const int32_t* adj, int64_t m, int32_t n_v, uint32_t* deg, int nrep) {
+    uint32_t* h = deg + (int64_t)(blockIdx.x % nrep) * n_v;
     GRID_STRIDE(i, m) {
         const int32_t v = adj[i];
-        if (v >= 0 && v < n_v) atomicAdd(&deg[v], 1u);
+        if (v >= 0 && v < n_v) atomicAdd(&h[v], 1u);
     }
 }
 
-__global__ void k_side_bins(const uint32_t* deg, int32_t n_v, unsigned long long* out) {
+__global__ __launch_bounds__(256) void k_side_bins(const uint32_t* deg, int32_t n_v, int nrep,
+                                                   unsigned long long* out) {
+    __shared__ unsigned long long red[256 / kWave];
     unsigned long long acc = 0;
-    GRID_STRIDE(i, n_v) acc += choose2_u64(deg[i]);
-    acc = wave_sum(acc);
-    if (lane_id() == 0 && acc) atomicAdd(&out[1], acc);
+    GRID_STRIDE(i, n_v) {
+        uint32_t d = 0;
+        for (int c = 0; c < nrep; ++c) d += deg[(int64_t)c * n_v + i];
+        acc += choose2_u64(d);
+    }
+    acc = block_sum<256>(acc, red);
+    if (threadIdx.x == 0 && acc) atomicAdd(&out[1], acc);
 }
 
 // graph id of every anchor of a batch (one workgroup per graph)
@@ -697,13 +709,15 @@ void launch_hist(const uint32_t* ids, int64_t n, uint32_t* deg, int64_t n_bins, 
     hipLaunchKernelGGL(k_hist_sum, dim3(grid_for(n_bins, 256)), dim3(256), 0, s, scratch, n_bins, nrep, deg);
 }
 
+// deg: nrep * n_v words
 void launch_side_wedges(const int32_t* off, int32_t n_u, const int32_t* adj, int64_t m, int32_t n_v, uint32_t* deg,
-                        unsigned long long* out, hipStream_t s) {
+                        int nrep, unsigned long long* out, hipStream_t s) {
     fill_u32(reinterpret_cast<uint32_t*>(out), 0u, 4, s);
-    fill_u32(deg, 0u, n_v, s);
-    if (n_u > 0) hipLaunchKernelGGL(k_side_rows, dim3(grid_for(n_u, 256)), dim3(256), 0, s, off, n_u, out);
-    if (m > 0) hipLaunchKernelGGL(k_side_hist, dim3(grid_for(m, 256)), dim3(256), 0, s, adj, m, n_v, deg);
-    if (n_v > 0) hipLaunchKernelGGL(k_side_bins, dim3(grid_for(n_v, 256)), dim3(256), 0, s, deg, n_v, out);
+    fill_u32(deg, 0u, (int64_t)nrep * n_v, s);
+    if (n_u > 0) hipLaunchKernelGGL(k_side_rows, dim3(grid_for(n_u, 256, kSideGrid)), dim3(256), 0, s, off, n_u, out);
+    if (m > 0) hipLaunchKernelGGL(k_side_hist, dim3(grid_for(m, 256)), dim3(256), 0, s, adj, m, n_v, deg, nrep);
+    if (n_v > 0)
+        hipLaunchKernelGGL(k_side_bins, dim3(grid_for(n_v, 256, kSideGrid)), dim3(256), 0, s, deg, n_v, nrep, out);
 }
 
 void launch_anchor_graph(const DevGraph* gr, int32_t n_graphs, uint32_t* agid, hipStream_t s) {
