@@ -286,9 +286,18 @@ struct Job {
 // times the other (a small side of hubs over a large side of low degrees
 // leaves nothing for the order to save, and its hubs' middles are all short
 // lists: 102 ms against 16 ms for the one-sided walk on 2.5M x 100K vertices
-// and 100M edges).
+// and 100M edges).  A total also needs a mean degree of at most kTopDegree
+// over both sides: denser lists give long slices, which the one-sided walk
+// reads without flattening, and their equal degrees leave the order little to
+// save.  us, one-sided and two-sided: 897 and 605 (20000 x 20000, 1M uniform
+// edges, mean 50), 949 and 863 (40000 x 20000, 1.5M power-law, 53), 3410 and
+// 3796 (200000 x 100000, 10M skewed, 71), 915 and 1203 (20000 x 20000, 2M
+// uniform, 100), 1371 and 3023 (the same, 4M).
 constexpr int64_t kTopRatio = 8;
+constexpr double kTopDegree = 64;
 bool top_fits(const Job& J) {
+    const double m = (double)J.m;
+    if (!J.pv && m * m > kTopDegree * kTopDegree * J.n_u * (double)J.n_v) return false;
     return J.m > 0 && J.m <= (1ll << 29) && J.n_u >= 1 && J.n_v >= 1 && J.n_u <= kTopRatio * J.n_v &&
            J.n_v <= kTopRatio * J.n_u;
 }

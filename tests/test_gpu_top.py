@@ -28,6 +28,9 @@ def gpu(ctx, g, **kw):
     return ctx.count(off, adj, sg, g.n_v, opts=bbc.options(**kw))
 
 
+IDLE = 2000  # vertices without an edge: totals of denser graphs take the one-sided walk
+
+
 def star_pairs(n_mid, n_end, seed, extra=0):
     """One U hub over n_mid V vertices, each of which also holds n_end U
     vertices: the hub walks about n_mid * n_end wedges; `extra` pendant edges
@@ -40,7 +43,7 @@ def star_pairs(n_mid, n_end, seed, extra=0):
         u.append(w)
         v.append(np.full(n_end, m))
     u, v = np.concatenate(u), np.concatenate(v)
-    return synth.from_edges(n_u + 1, n_mid + extra, u, v, np.where(rng.random(u.size) < 0.4, -1, 1))
+    return synth.from_edges(n_u + 1 + IDLE, n_mid + extra + IDLE, u, v, np.where(rng.random(u.size) < 0.4, -1, 1))
 
 
 # (middles, endpoints each): work around the bounds of the regimes (1,024 for a
@@ -60,7 +63,7 @@ def test_hashed_counter_overflow(ctx, mids, dense):
     rng = np.random.default_rng(mids)
     u, v = np.meshgrid(np.arange(dense), np.arange(mids), indexing="ij")
     u, v = u.ravel(), v.ravel()
-    g = synth.from_edges(dense + 5, mids + 3, u, v, np.where(rng.random(u.size) < 0.1, -1, 1))
+    g = synth.from_edges(dense + 5 + IDLE, mids + 3 + IDLE, u, v, np.where(rng.random(u.size) < 0.1, -1, 1))
     for light in (0, -1):
         assert gpu(ctx, g, wave_max_work=light) == oracle.count(g)
 
@@ -176,3 +179,9 @@ def test_per_vertex_power_law(ctx, n_u, n_v, m):
 @pytest.mark.parametrize("n,m", [(5000, 59_999), (5000, 60_000), (4999, 60_000), (5000, 350_000), (5000, 350_001)])
 def test_per_vertex_rule_edges(ctx, n, m):
     pv_check(ctx, synth.uniform_graph(n, n + 1 if m < 350_000 else n, m, 0.3, m))
+
+
+@pytest.mark.parametrize("m", [64_000, 64_001])
+def test_total_degree_edge(ctx, m):
+    g = synth.uniform_graph(1000, 1000, m, 0.3, m)
+    assert gpu(ctx, g) == oracle.count(g)
