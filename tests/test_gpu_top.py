@@ -185,3 +185,13 @@ def test_per_vertex_rule_edges(ctx, n, m):
 def test_total_degree_edge(ctx, m):
     g = synth.uniform_graph(1000, 1000, m, 0.3, m)
     assert gpu(ctx, g) == oracle.count(g)
+
+
+@pytest.mark.parametrize("schedule", ["dynamic", "static"])
+@pytest.mark.parametrize("per_cu", [0, 1])
+def test_many_heavy_anchors(ctx, schedule, per_cu):
+    """More than 512 anchors in the bands: a queue per XCD."""
+    g = synth.chung_lu_graph(70_000, 50_000, 1_200_000, 2.0, 2.0, 9000, 9000, 17, p_neg=0.3)
+    want = _WANT.get("heavy") or oracle.count(g)
+    _WANT["heavy"] = want
+    assert gpu(ctx, g, schedule=schedule, wg_per_cu=per_cu) == want
