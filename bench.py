@@ -40,16 +40,16 @@ HYBRID_WORKLOAD = "hybrid-2m-1m-50m-16x4096"
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, 8 TB/s
 INT8_PEAK_TOPS = 5000.0  # MI355X dense int8 matrix throughput, 5.0 POPS
 
-# HBM traffic of one call's wedge launches (both regimes) on the default
-# workload with the tuned configuration, from two rocprofv3 --pmc runs
+# HBM traffic of one call's walk launches (three regimes) on the default
+# workload with the library's defaults, from two rocprofv3 --pmc runs
 # (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch), each scaled by what the
 # counter reads for a 1 GiB device copy (fetch x 2.000, write x 1.000).
 # Valid only for the kernel sources it was taken on: the bench reports null
 # once their hash differs.
-KERNEL_SOURCES = ["paper_2601_17707_amd/csrc/wedge.hip", "paper_2601_17707_amd/csrc/bbc_internal.h"]
-MEASURED_TRAFFIC = dict(kernel="k_wedge", workload=WORKLOAD, bytes=53069999494,
-                        sources_sha256="659603a1ae3425f2f8dae4aab1e3c8d3dc3c5085f0ab163ad8a312593b902803",
-                        summary="profiles/k_wedge_powerlaw-1m-500k-20m_pmc.md")
+KERNEL_SOURCES = ["paper_2601_17707_amd/csrc/" + f for f in ("top_walk.hip", "top.h", "band.h", "bbc_internal.h")]
+MEASURED_TRAFFIC = dict(kernel="k_top_bands + k_top_hash + k_top_light", workload=WORKLOAD, bytes=27833814240,
+                        sources_sha256="b1b25222b483efc61d96af87ee1595054e3cde02a458039a322ebd80f524ff02",
+                        summary="profiles/k_top_powerlaw-1m-500k-20m_pmc.md")
 
 
 def measured_traffic(workload: str):
