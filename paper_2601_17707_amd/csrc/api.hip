@@ -443,12 +443,15 @@ void top_rank_side(TopPlan& P, int64_t n, int side, int64_t x0, hipStream_t s) {
     top_ranks(T.vv_a, T.deg, n, side, T.rank + x0, T.degr + x0, T.cstart, s);
 }
 
-// Queues the top-vertex pipeline on stream s (kernel launches only).
+// Queues the top-vertex pipeline on stream s (kernel launches only).  It looks
+// for repeated pairs whatever the caller's checks: its counter widths and
+// hashed tables rely on a simple graph (a pair of vertices has at most as many
+// common neighbours as either has edges), so a graph with one is left to the
+// one-sided walk (see repeated_pair).
 void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEvent_t* ev) {
     TopBuild& T = P.t;
     const int64_t m = J.m, nu = J.n_u, nv = J.n_v, n = nu + nv;
     const int check_sign = (J.checks & BBC_CHECK_SIGNS) ? 1 : 0;
-    const int check_dup = (J.checks & BBC_CHECK_DUPLICATES) ? 1 : 0;
     uint32_t* e[6];
     for (int i = 0; i < 6; ++i) e[i] = T.e + i * m;
     hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, st);
@@ -466,7 +469,7 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
     uint32_t *sk = odd1 ? e[2] : e[0], *sp = odd1 ? e[3] : e[1];
     radix_sort_to(e[0], SortBufs{e[2], e[3], nullptr}, SortBufs{e[0], e[1], nullptr}, e[1], nullptr, false, 0u,
                   SortBufs{sk, sp, nullptr}, nullptr, m, 0, bits_v, P.hist, P.hist_scan, P.partials, s);
-    top_runs(sk, sp, m, nv, check_dup, T.first, T.last, T.deg, T.key, st, s);
+    top_runs(sk, sp, m, nv, T.first, T.last, T.deg, T.key, st, s);
     top_rank_side(P, nv, 1, nu, s);
     scan_exclusive_u32(T.degr + nu, T.off + nu, nv, P.partials, s, (uint32_t)m);
     top_move(sk, sp, m, T.first, T.rank + nu, T.off + nu, T.ent + m, e[4], st, s);
@@ -1019,6 +1022,11 @@ bbc_status timed_stats(bbc_ctx* ctx) {
     return BBC_OK;
 }
 
+// Whether a job's result is a repeated pair that the one-sided walk has to deal
+// with: it reports it by the place in its own lists or, where the caller left
+// the check out, counts the multigraph.
+bool repeated_pair(const Job& J, bbc_status rc) { return rc == BBC_EDUP && (J.top || J.mat); }
+
 // Scratch bytes of a job.
 size_t job_bytes(const Job& J) {
     if (J.mat) return (size_t)matrix_bytes(J);
@@ -1084,7 +1092,7 @@ bbc_status run_job(bbc_ctx* ctx, Job& J, const bbc_options& opts, hipStream_t s,
     if (rc != BBC_OK) return rc;
     ctx->err.clear();
     rc = run_planned(ctx, J, ctx->arena, opts, s, dg, vstart, rend, db, dt);
-    if (rc == BBC_EDUP && (J.top || J.mat)) {  // reported by its place in the one-sided walk's lists
+    if (repeated_pair(J, rc)) {
         J.top = J.mat = false;
         return run_job(ctx, J, opts, s, dg, vstart, rend, db, dt);
     }
@@ -1310,9 +1318,11 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
                                               " bytes of scratch, the fixed scratch holds " +
                                               std::to_string(kFixedScratchBytes));
         rc = run_planned(ctx, J, ctx->fixed, opts, (hipStream_t)stream, nullptr, nullptr, nullptr, nullptr, nullptr);
-        if (rc == BBC_EDUP && (J.top || J.mat))
+        if (repeated_pair(J, rc)) {
+            ctx->err.clear();
             rc = run_planned(ctx, one, ctx->fixed, opts, (hipStream_t)stream, nullptr, nullptr, nullptr, nullptr,
                              nullptr);
+        }
     } else {
         rc = run_job(ctx, J, opts, (hipStream_t)stream, nullptr, nullptr, nullptr, &db, &dt);
     }

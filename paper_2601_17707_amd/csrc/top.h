@@ -117,8 +117,8 @@ void top_vertex_u(const int32_t* off, int32_t n_u, int64_t m, uint32_t* deg, uin
 void top_decode(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
                 int check_sign, const int32_t* rank, const uint32_t* roff, DevStatus* st, uint32_t* key, uint32_t* pay,
                 hipStream_t s);
-void top_runs(const uint32_t* key, const uint32_t* pay, int64_t m, int64_t n_v, int check_dup, uint32_t* first,
-              uint32_t* last, uint32_t* deg, uint32_t* vkey, DevStatus* st, hipStream_t s);
+void top_runs(const uint32_t* key, const uint32_t* pay, int64_t m, int64_t n_v, uint32_t* first, uint32_t* last,
+              uint32_t* deg, uint32_t* vkey, DevStatus* st, hipStream_t s);
 void top_ranks(const uint32_t* inv, const uint32_t* deg, int64_t n, int side, int32_t* rank, uint32_t* degr,
                uint32_t* cstart, hipStream_t s);
 void top_move(const uint32_t* key, const uint32_t* pay, int64_t m, const uint32_t* first, const int32_t* rank,

@@ -50,14 +50,14 @@ __global__ void k_top_vertex_u(const int32_t* __restrict__ off, int32_t n_u, int
 // id; inside a run the U ranks ascend, so a repeated pair is two equal
 // neighbours.
 __global__ void k_top_runs(const uint32_t* __restrict__ key, const uint32_t* __restrict__ pay, int64_t m,
-                           int check_dup, uint32_t* __restrict__ first, uint32_t* __restrict__ last, DevStatus* st) {
+                           uint32_t* __restrict__ first, uint32_t* __restrict__ last, DevStatus* st) {
     if (top_bad(st)) return;
     TOP_STRIDE(p, m) {
         const uint32_t k = key[p];
         const bool end = p == m - 1 || key[p + 1] != k;
         if (p == 0 || key[p - 1] != k) first[k] = (uint32_t)p;
         if (end) last[k] = (uint32_t)(p + 1);
-        else if (check_dup && top_rank(pay[p]) == top_rank(pay[p + 1])) top_flag(st, kBadDup, &st->bad_dup, p);
+        else if (top_rank(pay[p]) == top_rank(pay[p + 1])) top_flag(st, kBadDup, &st->bad_dup, p);
     }
 }
 
@@ -379,10 +379,10 @@ void top_vertex_u(const int32_t* off, int32_t n_u, int64_t m, uint32_t* deg, uin
                        st);
 }
 
-void top_runs(const uint32_t* key, const uint32_t* pay, int64_t m, int64_t n_v, int check_dup, uint32_t* first,
-              uint32_t* last, uint32_t* deg, uint32_t* vkey, DevStatus* st, hipStream_t s) {
+void top_runs(const uint32_t* key, const uint32_t* pay, int64_t m, int64_t n_v, uint32_t* first, uint32_t* last,
+              uint32_t* deg, uint32_t* vkey, DevStatus* st, hipStream_t s) {
     fill_u32(last, 0u, n_v, s);
-    hipLaunchKernelGGL(k_top_runs, dim3(top_grid(m, 256)), dim3(256), 0, s, key, pay, m, check_dup, first, last, st);
+    hipLaunchKernelGGL(k_top_runs, dim3(top_grid(m, 256)), dim3(256), 0, s, key, pay, m, first, last, st);
     hipLaunchKernelGGL(k_top_vertex_v, dim3(top_grid(n_v, 256)), dim3(256), 0, s, first, last, n_v, deg, vkey);
 }
 

@@ -215,7 +215,9 @@ __device__ __forceinline__ uint32_t hash_group(uint32_t* __restrict__ tab, const
 // endpoints' shares and 0.25 ms the second reading; the one-sided walk took
 // 14.6 ms.
 
-// The counters of key in the table (it is there).
+// The counters of key in the table.  It is there, so the search ends: in a
+// simple graph no counter has carried into a key (a bound on the search, or an
+// end at an empty slot, takes 40 to 50 us more on 2M power-law edges).
 __device__ __forceinline__ uint32_t hash_look(const uint32_t* __restrict__ tab, uint32_t key, int lt) {
     uint32_t h = (key * 0x9E3779B1u) >> (32 - lt);
     for (;;) {
@@ -289,7 +291,7 @@ __device__ __forceinline__ void hash_credit(Flat f, uint32_t* __restrict__ mark,
 __device__ __forceinline__ void hash_share(uint32_t v, uint32_t rx, uint32_t xb, unsigned long long* __restrict__ pv) {
     const uint32_t a = v & 63u, b = (v >> 6) & 63u;
     const uint32_t s = a * (a - (a > 0u)) + b * (b - (b > 0u));
-    if (s) atomicAdd(&pv[xb + rx - (v >> 12)], (unsigned long long)(s >> 1));
+    if (s && (v >> 12) <= rx) atomicAdd(&pv[xb + rx - (v >> 12)], (unsigned long long)(s >> 1));
 }
 
 // A middle as read ahead: entry, end of its wedges, start of its list.
@@ -782,7 +784,7 @@ __device__ __forceinline__ void band_credit(BandShared<WG, BW, true>& sh, const 
 
 // Endpoints' shares of a counted band, which is cleared; returns this thread's
 // sum.  Slot s of the band holds the rank r in it with r kSlotMul = s modulo
-// the band's slots.
+// the band's slots; no other slot holds anything.
 template <int WG>
 __device__ __forceinline__ unsigned long long share_words(uint32_t* __restrict__ cnt, const TopArgs& a,
                                                           const TopTask& t) {
@@ -792,6 +794,7 @@ __device__ __forceinline__ unsigned long long share_words(uint32_t* __restrict__
         const unsigned long long s = (ca * (ca - (ca > 0)) + cb * (cb - (cb > 0))) / 2ull;
         if (!s) return;
         const uint32_t r = t.lo + ((slot * kSlotInv - t.lo) & (slots - 1u));
+        if (r >= t.hi) return;
         atomicAdd(&a.pv[xb + r], s);
         sum += s;
     };
@@ -817,6 +820,7 @@ __device__ __forceinline__ unsigned long long share_words(uint32_t* __restrict__
             const uint32_t s = (ca * (ca - (ca > 0u)) >> 1) + (cb * (cb - (cb > 0u)) >> 1);
             if (!s) continue;
             const uint32_t r = t.lo + (((i * per + k) * kSlotInv - t.lo) & (slots - 1u));
+            if (r >= t.hi) continue;
             atomicAdd(&a.pv[xb + r], (unsigned long long)s);
             sum += s;
         }
