@@ -282,7 +282,8 @@ struct Job {
 };
 
 // Whether the job takes the top-vertex pipeline: positions of both sides'
-// lists (2 m) must fit 30 bits, and neither side may be more than kTopRatio
+// lists (2 m) must fit 30 bits, the ranks of a side the hashed slots' keys
+// (kTopMaxSide), and neither side may be more than kTopRatio
 // times the other (a small side of hubs over a large side of low degrees
 // leaves nothing for the order to save, and its hubs' middles are all short
 // lists: 102 ms against 16 ms for the one-sided walk on 2.5M x 100K vertices
@@ -299,7 +300,7 @@ bool top_fits(const Job& J) {
     const double m = (double)J.m;
     if (!J.pv && m * m > kTopDegree * kTopDegree * J.n_u * (double)J.n_v) return false;
     return J.m > 0 && J.m <= (1ll << 29) && J.n_u >= 1 && J.n_v >= 1 && J.n_u <= kTopRatio * J.n_v &&
-           J.n_v <= kTopRatio * J.n_u;
+           J.n_v <= kTopRatio * J.n_u && std::max(J.n_u, J.n_v) <= kTopMaxSide;
 }
 
 int64_t matrix_bytes(const Job& J) { return (int64_t)J.mat_rpad * J.mat_kpad; }

@@ -64,6 +64,21 @@ __device__ __forceinline__ int32_t band_lo(const TopBands& B, int32_t b) {
     return B.s3 + ((b - B.c3) << (B.lw - 1));
 }
 
+// Slots of the hashed tables: 32 bits, a key (anchor rank minus endpoint rank)
+// above two counters.  An anchor of rank below 2^20 leaves each counter 6 bits;
+// every four times as many ranks take one bit of each, down to 2 bits below
+// 2^28.  With 6 bits only, every anchor beyond 2^20 had to be counted in bands,
+// most of them empty, however few its wedges (they are the vertices of highest
+// degree): 2.5M x 1.25M vertices and 20M edges took 97.5 ms (uniform) and
+// 127 ms (power law) instead of 3.1 and 10.5 ms; the one-sided walk, whose wave
+// regime ends at 2^20 ranks too, takes 20 and 71 ms.
+constexpr uint32_t kSlotBits = 6, kSlotMinBits = 2;
+constexpr int64_t kTopMaxSide = 1ll << (32 - 2 * kSlotMinBits);
+__host__ __device__ __forceinline__ uint32_t slot_bits(uint32_t rank) {  // per counter
+    const uint32_t b = (uint32_t)__builtin_clz(rank | 1u) >> 1;
+    return b < kSlotBits ? b : kSlotBits;
+}
+
 // Schedule classes (sort key of the anchors): descending work class, then
 // the wave regime, then anchors with fewer than two wedges.
 constexpr uint32_t kTopLight = 254, kTopNone = 255;

@@ -333,9 +333,9 @@ __global__ __launch_bounds__(256) void k_top_work(const uint32_t* __restrict__ x
 }
 
 // Schedule key of each vertex (see kTopLight): anchors of the workgroup
-// regime by descending work class (those with 2^20 ranks or more below them
-// in the bands' classes), then the wave regime (at most light_w wedges and 63
-// middles), then anchors without a pair.
+// regime by descending work class, then the wave regime (at most light_w
+// wedges, and as many middles as a slot's counter holds, so that none can
+// overflow: 63 below rank 2^20), then anchors without a pair.
 __global__ void k_top_schedule(const unsigned long long* __restrict__ work, const uint32_t* __restrict__ kx,
                                int64_t n_u, int64_t n, uint32_t light_w, uint32_t* __restrict__ skey,
                                const DevStatus* st) {
@@ -346,10 +346,9 @@ __global__ void k_top_schedule(const unsigned long long* __restrict__ work, cons
             const unsigned long long w = work[x];
             const uint32_t k = kx[x];
             if (w >= 2 && k >= 2) {
-                const bool near = (x >= n_u ? x - n_u : x) < (1ll << kLightKeyBits);  // endpoint keys fit the hashed slots
-                uint32_t c = degree_class(w > 0x7fffffffull ? 0x7fffffffu : (uint32_t)w);
-                if (!near && c < degree_class(kTierWork[0])) c = degree_class(kTierWork[0]);
-                key = near && w <= light_w && k <= (uint32_t)kLightMaxDeg ? kTopLight : 231u - c;
+                const uint32_t most = (1u << slot_bits((uint32_t)(x >= n_u ? x - n_u : x))) - 1u;
+                const uint32_t c = degree_class(w > 0x7fffffffull ? 0x7fffffffu : (uint32_t)w);
+                key = w <= light_w && k <= most ? kTopLight : 231u - c;
             }
         }
         skey[x] = key;

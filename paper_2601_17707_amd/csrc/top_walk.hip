@@ -135,10 +135,20 @@ __device__ __forceinline__ BandFields band_fields(int mode, uint32_t words) {
     return f;
 }
 
+// Layout of an anchor's hashed slots (see slot_bits), the same for every lane:
+// bits per counter, the largest counter, the largest key.
+struct SlotLayout {
+    uint32_t cb, ones, keys;
+};
+__device__ __forceinline__ SlotLayout slot_layout(uint32_t rank) {
+    const uint32_t cb = slot_bits(rank);
+    return SlotLayout{cb, (1u << cb) - 1u, ~0u >> (2u * cb)};
+}
+
 // Hashed counting: a slot holds the endpoint's key (anchor rank - endpoint
-// rank, 1 .. 2^20 - 1) above two 6-bit counters; an insert returns the
-// counter's value before it, which is its share of C(x, 2).  A counter that
-// passes 63 is reported (`full`): the caller then counts the anchor in bands.
+// rank, from 1) above two counters; an insert returns the counter's value
+// before it, which is its share of C(x, 2).  A counter that passes its width
+// is reported (`full`): the caller then counts the anchor in bands.
 // LOCK: all of a lane's positions probe in lock step, so that their LDS round
 // trips overlap (a slot, once claimed, keeps its key, so probing on meets the
 // same slots in any order).  For the waves that share a table: 745 us instead
@@ -148,13 +158,13 @@ __device__ __forceinline__ BandFields band_fields(int mode, uint32_t words) {
 // lt: log2 of the slots in use, at least twice the wedges, so every probe ends.
 template <int GP, bool LOCK>
 __device__ __forceinline__ uint32_t hash_group(uint32_t* __restrict__ tab, const Group<GP>& g, uint32_t rx, int lt,
-                                               bool& full) {
+                                               const SlotLayout& sl, bool& full) {
     uint32_t key[GP], sh[GP], h[GP];
     uint32_t pend = 0;  // positions still probing
 #pragma unroll
     for (int i = 0; i < GP; ++i) {
-        key[i] = (rx - g.x[i]) & ((1u << kLightKeyBits) - 1u);
-        sh[i] = ((g.x[i] ^ g.tv[i]) >> 31) * 6u;
+        key[i] = (rx - g.x[i]) & sl.keys;
+        sh[i] = (uint32_t)((int32_t)(g.x[i] ^ g.tv[i]) >> 31) & sl.cb;
         h[i] = (key[i] * 0x9E3779B1u) >> (32 - lt);
         pend |= (i < g.nv ? 1u : 0u) << i;
     }
@@ -164,11 +174,11 @@ __device__ __forceinline__ uint32_t hash_group(uint32_t* __restrict__ tab, const
         for (int i = 0; i < GP; ++i) {
             if (!((pend >> i) & 1u)) continue;
             for (;;) {
-                const uint32_t old = atomicCAS(&tab[h[i]], 0u, (key[i] << 12) | (1u << sh[i]));
+                const uint32_t old = atomicCAS(&tab[h[i]], 0u, (key[i] << (2u * sl.cb)) | (1u << sh[i]));
                 if (old == 0u) break;
-                if ((old >> 12) == key[i]) {
-                    const uint32_t c = (atomicAdd(&tab[h[i]], 1u << sh[i]) >> sh[i]) & 63u;
-                    if (c == 63u) full = true;
+                if ((old >> (2u * sl.cb)) == key[i]) {
+                    const uint32_t c = (atomicAdd(&tab[h[i]], 1u << sh[i]) >> sh[i]) & sl.ones;
+                    if (c == sl.ones) full = true;
                     acc += c;
                     break;
                 }
@@ -182,21 +192,21 @@ __device__ __forceinline__ uint32_t hash_group(uint32_t* __restrict__ tab, const
 #pragma unroll
         for (int i = 0; i < GP; ++i) {
             old[i] = 0u;
-            if ((pend >> i) & 1u) old[i] = atomicCAS(&tab[h[i]], 0u, (key[i] << 12) | (1u << sh[i]));
+            if ((pend >> i) & 1u) old[i] = atomicCAS(&tab[h[i]], 0u, (key[i] << (2u * sl.cb)) | (1u << sh[i]));
         }
 #pragma unroll
         for (int i = 0; i < GP; ++i) {
             v[i] = 0u;
-            if (old[i] != 0u && (old[i] >> 12) == key[i]) v[i] = atomicAdd(&tab[h[i]], 1u << sh[i]);
+            if (old[i] != 0u && (old[i] >> (2u * sl.cb)) == key[i]) v[i] = atomicAdd(&tab[h[i]], 1u << sh[i]);
         }
         uint32_t next = 0;
 #pragma unroll
         for (int i = 0; i < GP; ++i) {
-            const bool other = old[i] != 0u && (old[i] >> 12) != key[i];
+            const bool other = old[i] != 0u && (old[i] >> (2u * sl.cb)) != key[i];
             next |= (other ? 1u : 0u) << i;
             h[i] = (h[i] + 1u) & ((1u << lt) - 1u);  // where another key was met
-            const uint32_t c = (v[i] >> sh[i]) & 63u;
-            if (c == 63u) full = true;
+            const uint32_t c = (v[i] >> sh[i]) & sl.ones;
+            if (c == sl.ones) full = true;
             acc += c;
         }
         pend &= next;
@@ -218,11 +228,12 @@ __device__ __forceinline__ uint32_t hash_group(uint32_t* __restrict__ tab, const
 // The counters of key in the table.  It is there, so the search ends: in a
 // simple graph no counter has carried into a key (a bound on the search, or an
 // end at an empty slot, takes 40 to 50 us more on 2M power-law edges).
-__device__ __forceinline__ uint32_t hash_look(const uint32_t* __restrict__ tab, uint32_t key, int lt) {
+__device__ __forceinline__ uint32_t hash_look(const uint32_t* __restrict__ tab, uint32_t key, int lt,
+                                              const SlotLayout& sl) {
     uint32_t h = (key * 0x9E3779B1u) >> (32 - lt);
     for (;;) {
         const uint32_t v = tab[h];
-        if ((v >> 12) == key) return v;
+        if ((v >> (2u * sl.cb)) == key) return v;
         h = (h + 1u) & ((1u << lt) - 1u);
     }
 }
@@ -260,8 +271,8 @@ __device__ __forceinline__ void slice_add(uint32_t* __restrict__ ys, const uint3
 template <int GP>
 __device__ __forceinline__ void hash_credit(Flat f, uint32_t* __restrict__ mark, const uint32_t* __restrict__ stab,
                                             const uint32_t* __restrict__ ent, const uint32_t* __restrict__ tab, uint32_t rx,
-                                            int lt, uint32_t* __restrict__ ys, unsigned long long* __restrict__ pv,
-                                            uint32_t y) {
+                                            int lt, const SlotLayout& sl, uint32_t* __restrict__ ys,
+                                            unsigned long long* __restrict__ pv, uint32_t y) {
     const int lane = lane_id();
     f.carry = 0;
     for (int32_t j0 = 0; j0 < f.total; j0 += GP * kWave) {
@@ -272,8 +283,8 @@ __device__ __forceinline__ void hash_credit(Flat f, uint32_t* __restrict__ mark,
         for (int i = 0; i < GP; ++i) {
             give[i] = 0;
             if (i >= g.nv) continue;
-            const uint32_t v = hash_look(tab, (rx - g.x[i]) & ((1u << kLightKeyBits) - 1u), lt);
-            give[i] = ((v >> (((g.x[i] ^ g.tv[i]) >> 31) * 6u)) & 63u) - 1u;
+            const uint32_t v = hash_look(tab, (rx - g.x[i]) & sl.keys, lt, sl);
+            give[i] = ((v >> ((uint32_t)((int32_t)(g.x[i] ^ g.tv[i]) >> 31) & sl.cb)) & sl.ones) - 1u;
         }
         slice_add<GP>(ys, g.sl, give);
     }
@@ -288,10 +299,11 @@ __device__ __forceinline__ void hash_credit(Flat f, uint32_t* __restrict__ mark,
 
 // Endpoints' shares of slot v of a table (anchor rank rx, first vertex of its
 // side xb).
-__device__ __forceinline__ void hash_share(uint32_t v, uint32_t rx, uint32_t xb, unsigned long long* __restrict__ pv) {
-    const uint32_t a = v & 63u, b = (v >> 6) & 63u;
+__device__ __forceinline__ void hash_share(uint32_t v, uint32_t rx, uint32_t xb, const SlotLayout& sl,
+                                           unsigned long long* __restrict__ pv) {
+    const uint32_t a = v & sl.ones, b = (v >> sl.cb) & sl.ones, key = v >> (2u * sl.cb);
     const uint32_t s = a * (a - (a > 0u)) + b * (b - (b > 0u));
-    if (s && (v >> 12) <= rx) atomicAdd(&pv[xb + rx - (v >> 12)], (unsigned long long)(s >> 1));
+    if (s && key <= rx) atomicAdd(&pv[xb + rx - key], (unsigned long long)(s >> 1));
 }
 
 // A middle as read ahead: entry, end of its wedges, start of its list.
@@ -951,7 +963,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
 // (in bands they held a few dozen wedges each), and slices need no index: a
 // middle's wedges are its whole prefix.  Chunks of CH middles, highest first,
 // go to the waves in turn; the next anchor is read while this one's table is
-// cleared.  An anchor with a counter past 63 is left to the bands (kernel
+// cleared.  An anchor with a counter past its width is left to the bands (kernel
 // k_top_bands runs after this one).
 template <int WG, int LTMAX, bool FULL>
 struct HashShared {
@@ -1036,6 +1048,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
         if (t.k == 0) break;
         if (tid == 0) take(sh.task[it ^ 1u]);
         const uint32_t n_ch = t.k <= NW * CH0 ? (t.k + CH0 - 1u) / CH0 : NW + (t.k - NW * CH0 + CH - 1u) / CH;
+        const SlotLayout sl = slot_layout(t.r);
         uint32_t s = 0;
         bool full = false;
         for (uint32_t c = w0; c < n_ch; c += NW) {
@@ -1049,12 +1062,12 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
                 j0 += GP * kWave;
                 if (j0 < f.total) flat_load<GP>(f, fl.mark, fl.tab, a.ent, j0, gb);
                 __builtin_amdgcn_sched_barrier(0);
-                s += hash_group<GP, true>(sh.tab, ga, t.r, t.mode, full);
+                s += hash_group<GP, true>(sh.tab, ga, t.r, t.mode, sl, full);
                 if (j0 >= f.total) break;
                 j0 += GP * kWave;
                 if (j0 < f.total) flat_load<GP>(f, fl.mark, fl.tab, a.ent, j0, ga);
                 __builtin_amdgcn_sched_barrier(0);
-                s += hash_group<GP, true>(sh.tab, gb, t.r, t.mode, full);
+                s += hash_group<GP, true>(sh.tab, gb, t.r, t.mode, sl, full);
             }
         }
         if (full) sh.full = 1u;
@@ -1068,7 +1081,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
                     mids(t, c, m, has);
                     Flat f;
                     flat_begin(f, fl.tab, m.ms, has ? (int32_t)(m.cr - m.ms) : 0, m.e);
-                    hash_credit<GP>(f, fl.mark, fl.tab, a.ent, sh.tab, t.r, t.mode, sh.ys[wave], a.pv,
+                    hash_credit<GP>(f, fl.mark, fl.tab, a.ent, sh.tab, t.r, t.mode, sl, sh.ys[wave], a.pv,
                                     yb + top_rank(m.e));
                 }
                 const unsigned long long w = wave_sum((unsigned long long)s);
@@ -1077,7 +1090,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
                 if (tid == 0) sh.any = 0;
                 for (int i = tid; i < (1 << t.mode); i += WG) {
                     const uint32_t v = sh.tab[i];
-                    if (v) hash_share(v, t.r, (uint32_t)a.n_u - yb, a.pv);
+                    if (v) hash_share(v, t.r, (uint32_t)a.n_u - yb, sl, a.pv);
                 }
                 __syncthreads();
             }
@@ -1100,7 +1113,8 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
 
 // ------------------------------------------------------------ wave regime
 //
-// Light anchors (at most kLightMaxWork wedges, 63 middles): one wave each, a
+// Light anchors (at most kLightMaxWork wedges; at most 63 middles, see
+// k_top_schedule): one wave each, a
 // hashed table of 2048 slots per wave, no barrier.  The wave reads ahead: an
 // anchor's place in the schedule three anchors before it is counted, its list
 // range two before, its middles one before, and its first group of endpoints
@@ -1195,26 +1209,27 @@ __global__ __launch_bounds__(kTopLightWG, 4) void k_top_light(TopArgs a) {
             head(x3, h2);
             x3 = place(p + 4);
             __builtin_amdgcn_sched_barrier(0);
-            bool full = false;  // at most 63 middles: no counter passes 63
+            bool full = false;  // no more middles than a counter holds: none overflows
+            const SlotLayout sl = slot_layout((uint32_t)__builtin_amdgcn_readfirstlane((int)rx));
             // slots for twice the wedges: most anchors have few, and clearing
             // the whole table took longer than counting them
             const int lt = max(8, 33 - __clz(f[b].total - 1));
-            uint32_t s = hash_group<GP, false>(tab, gr[b], rx, lt, full);
+            uint32_t s = hash_group<GP, false>(tab, gr[b], rx, lt, sl, full);
             for (int32_t j0 = GP * kWave; j0 < f[b].total; j0 += GP * kWave) {
                 flat_load<GP>(f[b], mark, flat[wave][b].tab, a.ent, j0, gr[b]);
-                s += hash_group<GP, false>(tab, gr[b], rx, lt, full);
+                s += hash_group<GP, false>(tab, gr[b], rx, lt, sl, full);
             }
             if constexpr (FULL) {
                 if (__any(s != 0u)) {
                     const uint32_t yb = x < (uint32_t)a.n_u ? (uint32_t)a.n_u : 0u;
                     const uint32_t e = a.ent[own.a0 + ((uint32_t)lane < own.k ? (uint32_t)lane : 0u)];
-                    hash_credit<GP>(f[b], mark, flat[wave][b].tab, a.ent, tab, rx, lt, ys[wave], a.pv,
+                    hash_credit<GP>(f[b], mark, flat[wave][b].tab, a.ent, tab, rx, lt, sl, ys[wave], a.pv,
                                     yb + top_rank(e));
                     const unsigned long long w = wave_sum((unsigned long long)s);
                     if (lane == 0) atomicAdd(&a.pv[x], w);
                     for (int i = lane; i < (1 << lt); i += kWave) {
                         const uint32_t v = tab[i];
-                        if (v) hash_share(v, rx, (uint32_t)a.n_u - yb, a.pv);
+                        if (v) hash_share(v, rx, (uint32_t)a.n_u - yb, sl, a.pv);
                     }
                     __builtin_amdgcn_wave_barrier();
                 }
