@@ -94,7 +94,8 @@ constexpr uint32_t kTierWork[kTopTiers] = {16384, 4096};
 // regime.  n_extra anchors whose hashed counters overflowed join the bands.
 struct TopCounts {
     uint32_t n_tier[kTopTiers + 1], n_walk, nb_max, n_extra;
-    unsigned int queue[8], queue_hash[kTopTiers];
+    unsigned long long queue[8];  // an anchor has a task per band: more than 2^32 on the widest sides
+    unsigned int queue_hash[kTopTiers];
 };
 
 constexpr uint32_t kTopFewBands = 16;  // up to this many bands, every list has index entries

@@ -890,11 +890,11 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
                 if (a.statik || tried == nq) return;
                 ++tried;
                 queue = queue + 1u == nq ? 0u : queue + 1u;
-                ahead = (unsigned long long)groups(queue) + atomicAdd(&a.tc->queue[queue], 1u);
+                ahead = groups(queue) + atomicAdd(&a.tc->queue[queue], 1ull);
             }
             const unsigned long long i = ahead;
             const uint32_t own = queue;
-            ahead = a.statik ? i + groups(own) : (unsigned long long)groups(own) + atomicAdd(&a.tc->queue[own], 1u);
+            ahead = a.statik ? i + groups(own) : groups(own) + atomicAdd(&a.tc->queue[own], 1ull);
             const uint32_t q = nq == 1u ? (uint32_t)(i % n_all) : own + nq * (uint32_t)(i / nb_max);
             const uint32_t id = q < n_split ? a.order[q] : a.extra[q - n_split];
             const TopAnchor x = top_anchor(a, id);
