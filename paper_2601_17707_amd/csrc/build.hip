@@ -456,9 +456,15 @@ __global__ void k_check_dup(const uint32_t* ckey, const uint32_t* packed, int64_
 // a wave sums runs of equal rank with a segmented scan and adds each run
 // once.  st->wedges receives the sum over centres of C(deg, 2), st->walked
 // the wedges the walk visits.  Bound by the latency of the random reads per
-// entry: 20M edges of 2.5M x 100K vertices take 360 us with two entries a
-// thread and as many workgroups as that gives, 387 us with four on 4096.
+// entry and, where anchors hold hundreds of entries, by the atomics: workgroups
+// in flight together are neighbours and add to the same few anchors, one after
+// the other.  There 4096 workgroups, each going over the whole array, drift
+// apart; shorter lists gain from as many workgroups as the entries give.  us,
+// 4096 workgroups and up to 65536: 1140 and 1483 to 2047 (100M edges, mean
+// list 1000), 303 and 364 (20M edges, 200), 221 and 219 (8.4M, 33), 310 and
+// 278 (1500 graphs, 42M, 14).
 constexpr int kWorkItems = 2;  // entries per thread whose loads are in flight together
+constexpr int64_t kWorkLongLists = 128;
 __global__ __launch_bounds__(256) void k_work(const uint32_t* __restrict__ apack, const int32_t* __restrict__ acent,
                                               const int32_t* __restrict__ back, const uint32_t* __restrict__ coff,
                                               int64_t m, unsigned long long* __restrict__ work, DevStatus* st,
@@ -744,9 +750,10 @@ void launch_work(const uint32_t* apack, const int32_t* acent, const int32_t* bac
                  const int64_t* rank_end, uint32_t light_w, DevStatus* st, const HybridView& hv, hipStream_t s) {
     if (n_s <= 0) return;
     fill_bytes(work, n_s * 8, s);
+    const int cap = m >= kWorkLongLists * n_s ? 4096 : 65536;
     if (m > 0)
-        hipLaunchKernelGGL(k_work, dim3(grid_for(m, 256 * kWorkItems, 65536)), dim3(256), 0, s, apack, acent, back, coff, m, work,
-                           st, hv);
+        hipLaunchKernelGGL(k_work, dim3(grid_for(m, 256 * kWorkItems, cap)), dim3(256), 0, s, apack, acent, back, coff,
+                           m, work, st, hv);
     hipLaunchKernelGGL(k_work_keys, dim3(grid_for(n_s, 256)), dim3(256), 0, s, work, n_s, key, aoff, agraph,
                        rank_end, hv.ablk1, light_w, st);
 }
