@@ -13,6 +13,7 @@
 
 #include "../../include/bbc.h"
 #include "bbc_internal.h"
+#include "route.h"
 #include "top.h"
 
 namespace bbc {
@@ -278,32 +279,10 @@ struct Job {
     int top_words = 0, top_wg = 0, top_grid = 0, light_grid = 0, n_cu = 0;
     // sign matrix of the whole graph and its products (small sides)
     bool mat = false;
-    int32_t mat_tile = 0, mat_rpad = 0, mat_kpad = 0;
+    MatrixShape mat_shape{};
 };
 
-// Whether the job takes the top-vertex pipeline: positions of both sides'
-// lists (2 m) must fit 30 bits, the ranks of a side the hashed slots' keys
-// (kTopMaxSide), and neither side may be more than kTopRatio
-// times the other (a small side of hubs over a large side of low degrees
-// leaves nothing for the order to save, and its hubs' middles are all short
-// lists: 102 ms against 16 ms for the one-sided walk on 2.5M x 100K vertices
-// and 100M edges).  A total also needs a mean degree of at most kTopDegree
-// over both sides: denser lists give long slices, which the one-sided walk
-// reads without flattening, and their equal degrees leave the order little to
-// save.  us, one-sided and two-sided: 897 and 605 (20000 x 20000, 1M uniform
-// edges, mean 50), 949 and 863 (40000 x 20000, 1.5M power-law, 53), 3410 and
-// 3796 (200000 x 100000, 10M skewed, 71), 915 and 1203 (20000 x 20000, 2M
-// uniform, 100), 1371 and 3023 (the same, 4M).
-constexpr int64_t kTopRatio = 8;
-constexpr double kTopDegree = 64;
-bool top_fits(const Job& J) {
-    const double m = (double)J.m;
-    if (!J.pv && m * m > kTopDegree * kTopDegree * J.n_u * (double)J.n_v) return false;
-    return J.m > 0 && J.m <= (1ll << 29) && J.n_u >= 1 && J.n_v >= 1 && J.n_u <= kTopRatio * J.n_v &&
-           J.n_v <= kTopRatio * J.n_u && std::max(J.n_u, J.n_v) <= kTopMaxSide;
-}
-
-int64_t matrix_bytes(const Job& J) { return (int64_t)J.mat_rpad * J.mat_kpad; }
+int64_t matrix_bytes(const Job& J) { return (int64_t)J.mat_shape.rpad * J.mat_shape.kpad; }
 
 // All device buffers of one pass, carved from an arena in a fixed order.
 struct Plan {
@@ -514,9 +493,9 @@ void enqueue_matrix(const Job& J, int8_t* mat, DevStatus* st, hipStream_t s, hip
     hipLaunchKernelGGL(k_status_init, dim3(1), dim3(kStatusThreads), 0, s, st);
     if (ev) (void)hipEventRecord(ev[0], s);
     launch_matrix_build(J.off, J.adj, J.sg, J.n_u, J.n_v, J.m, J.s_is_u ? 1 : 0, check_sign, mat, matrix_bytes(J),
-                        J.mat_kpad, st, s);
+                        J.mat_shape.kpad, st, s);
     if (ev) (void)hipEventRecord(ev[1], s);
-    launch_matrix_pairs(mat, (int32_t)J.n_s, J.mat_rpad, J.mat_kpad, J.mat_tile, st, s);
+    launch_matrix_pairs(mat, (int32_t)J.n_s, J.mat_shape.rpad, J.mat_shape.kpad, J.mat_shape.tile, st, s);
     if (ev) (void)hipEventRecord(ev[2], s);
 }
 
@@ -698,24 +677,8 @@ void set_regimes(Job& J, const bbc_options& o, bool full) {
 // smaller sides get two narrower workgroups per CU.
 constexpr int kTopWords = 32768, kTopWG = 1024, kTopSmallWords = 16384, kTopSmallWG = 512;
 
-// Whether a per-vertex count takes the top-vertex pipeline: its launches and
-// second readings pay from 60K edges, and on a smaller side of 5000 to 32767
-// vertices (at most two of the one-sided walk's wide bands) only up to a mean
-// degree of 70 over both sides.  us, one-sided and top-vertex: 313 and 372
-// (5000 x 2500, 75K edges), 459 and 407 (8000 x 5000, 60K), 835 and 593 (23117
-// x 9041, 301K), 2900 and 2181 (66000 x 13000, 2M: mean 68), 1188 and 1420
-// (30000 x 6000, 1M: mean 75), 5296 and 11000 (20000 x 20000, 4M, uniform),
-// 10176 and 5411 (80000 x 40000, 8M, uniform), 46266 and 12959 (the same,
-// power law), 15280 and 2046 (100003 x 50021, 2M).
-bool top_full_fits(const Job& J) {
-    const int64_t side = std::min(J.n_u, J.n_v);
-    const double m = (double)J.m;
-    return J.m >= 60000 && (side >= 32768 || (side >= 5000 && m * m <= 70.0 * 70.0 * J.n_u * (double)J.n_v));
-}
-
 // Top-vertex pipeline of a job whose sizes and options are set.
 void set_top(const bbc_ctx* ctx, Job& J, const bbc_options& o) {
-    if (!top_fits(J)) return;
     J.top = true;
     const bool fixed = !J.pv && (o.band_words || o.wg_size);
     const bool large = !J.pv && std::max(J.n_u, J.n_v) >= 16 * kTopWords;
@@ -725,37 +688,6 @@ void set_top(const bbc_ctx* ctx, Job& J, const bbc_options& o) {
     J.n_cu = ctx->n_cu;
     J.light_grid = ctx->n_cu * top_light_blocks_per_cu();
     J.light_w = std::min(J.light_w, kLightMaxWork);
-}
-
-// Matrix count of a job whose sizes are set: the signed adjacency matrix S of
-// the whole graph as bytes, and the pair terms of S S^T and |S| |S|^T on the
-// matrix cores: no ranks, lists or schedule, and five launches instead of
-// about forty.  Its time in us is close to the sum of 40 for the launches and
-// the status copy, the clearing (3 MB per us), the products (1.2 to 2.3 Gops
-// per us with 64- and 128-row tiles) and an atomic per edge (25K per us); the
-// walks take at least 120, growing to 300 at 30K edges, and 0.1 per 1000
-// edges, whatever the degrees (more the more wedges they have).  Measured,
-// matrix against walk: 32 and 156 us (30 x 20, 100 edges), 65 and 246 (2000 x
-// 1000, 20K), 178 and 337 (5000 x 5000, 75K), 289 and 341 (10000 x 5000,
-// 150K), 913 and 348 (10000 x 10000, 200K), 151 and 1491 (3000 x 3000, 2M),
-// 322 and 354 (40000 x 2000, 400K).  The line lies 15% below the walk's.  The
-// output tiles have 64 rows where the larger ones would number less than one
-// per CU (103 and 114 us at 2500 rows, 101 and 92 us at 3000).
-constexpr int64_t kMatMaxBytes = 64ll << 20;  // a graph of few edges should not grow the arena beyond that
-void set_matrix(Job& J, int n_cu) {
-    // one pair's counts fit 16 bits; a repeated edge is not counted twice here
-    if (J.m <= 0 || J.n_s < 2 || J.n_c < 1 || J.n_c > 65535 || !(J.checks & BBC_CHECK_DUPLICATES)) return;
-    const int64_t t = (J.n_s + 127) / 128;
-    const int32_t tile = t * (t + 1) / 2 < n_cu ? 64 : 128;
-    const int64_t rpad = (J.n_s + tile - 1) / tile * tile, kpad = (J.n_c + 63) / 64 * 64;
-    const double bytes = (double)rpad * kpad, ops = 2.0 * rpad * bytes, m = (double)J.m;
-    const double matrix = 40 + bytes / 3e6 + ops / (tile == 64 ? 1.2e9 : 2.2e9) + m / 25e3;
-    const double walk = 0.85 * (120 + 180 * std::min(1.0, m / 30e3) + m / 10e3);
-    if (bytes > kMatMaxBytes || matrix > walk) return;
-    J.mat = true;
-    J.mat_tile = tile;
-    J.mat_rpad = (int32_t)rpad;
-    J.mat_kpad = (int32_t)kpad;
 }
 
 bool side_is_u(int side, int32_t n_u, int32_t n_v) { return side == BBC_SIDE_U || (side == BBC_SIDE_AUTO && n_u < n_v); }
@@ -1301,10 +1233,11 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
         rc = block_job(ctx, opts, J, db, dt);
         if (rc != BBC_OK) return rc;
     }
-    if (opts.n_blocks == 0) {
-        if (open && !full) set_matrix(J, ctx->n_cu);
-        if (!J.mat && (!full || (open && top_full_fits(J)))) set_top(ctx, J, opts);
-    }
+    RouteInput in{n_u, n_v, n_edges, J.s_is_u, full, opts.n_blocks > 0, !open,
+                  (opts.checks & BBC_CHECK_DUPLICATES) != 0, ctx->n_cu};
+    const Route route = choose_route(in, &J.mat_shape);
+    J.mat = route == Route::kMatrix;
+    if (route == Route::kTwoSided) set_top(ctx, J, opts);
     if (fixed) {
         const auto fits = [&](size_t b) { return b <= kFixedScratchBytes && (ctx->limit <= 0 || b <= (size_t)ctx->limit); };
         Job one = J;

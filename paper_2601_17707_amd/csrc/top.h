@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "bbc_internal.h"
+#include "route.h"
 
 namespace bbc {
 
@@ -73,7 +74,7 @@ __device__ __forceinline__ int32_t band_lo(const TopBands& B, int32_t b) {
 // 127 ms (power law) instead of 3.1 and 10.5 ms; the one-sided walk, whose wave
 // regime ends at 2^20 ranks too, takes 20 and 71 ms.
 constexpr uint32_t kSlotBits = 6, kSlotMinBits = 2;
-constexpr int64_t kTopMaxSide = 1ll << (32 - 2 * kSlotMinBits);
+static_assert(kTopMaxSide == 1ll << (32 - 2 * kSlotMinBits), "the widest side's keys fit a slot");
 __host__ __device__ __forceinline__ uint32_t slot_bits(uint32_t rank) {  // per counter
     const uint32_t b = (uint32_t)__builtin_clz(rank | 1u) >> 1;
     return b < kSlotBits ? b : kSlotBits;
