@@ -391,7 +391,6 @@ struct TopPlan {
         t.thr = c.take<uint32_t>(n);
         t.kx = c.take<uint32_t>(n);
         t.order = c.take<uint32_t>(n);
-        t.skey = c.take<uint32_t>(n);
         t.first = c.take<uint32_t>(nv);
         t.last = c.take<uint32_t>(nv);
         t.work = c.take<unsigned long long>(n);
@@ -405,7 +404,8 @@ struct TopPlan {
         t.icnt = c.take<uint32_t>(n);
         t.ioff = c.take<uint32_t>(n + 1);
         t.row = c.take<uint2>(n);
-        t.idx = c.take<uint32_t>(2 * m + (kTopFewBands + 1) * n);
+        const int lw = band_log(J.top_words, std::max(nu, nv));
+        t.idx = c.take<uint32_t>(index_words(nu, nv, m, lw) + index_words(nv, nu, m, lw));
         const int64_t hs = (int64_t)radix_hist_size(std::max(m, n));
         hist = c.take<uint32_t>(hs);
         hist_scan = c.take<uint32_t>(hs + 1);
@@ -461,12 +461,7 @@ void enqueue_top(const Job& J, TopPlan& P, DevStatus* st, hipStream_t s, hipEven
                   (uint32_t)m, SortBufs{xkey, T.ent, T.cross}, reinterpret_cast<int32_t*>(T.cross), m, 0, bits_u, P.hist,
                   P.hist_scan, P.partials, s);
 
-    const int64_t n_max = std::max(nu, nv);
-    int lw = 0;
-    while ((2 << lw) <= J.top_words) ++lw;
-    // narrower bands where a side holds few, so that the bands of the
-    // heaviest vertices spread over the chip
-    while (lw > 9 && ((int64_t)16 << lw) > n_max) --lw;
+    const int lw = band_log(J.top_words, std::max(nu, nv));
     top_vertices(T.degr, T.cstart, nu, nv, J.s_is_u ? 1 : 0, lw, T.thr, T.kx, T.work, T.bands, T.tc, st, s);
     top_index(T.off, nu, n, T.bands, T.icnt, T.ioff, T.row, P.partials, st, s);
     uint32_t* mbase = e[1];  // and e[2]
@@ -620,6 +615,21 @@ void enqueue(const Job& J, Plan& P, DevStatus* st, hipStream_t s, hipEvent_t* ev
     if (ev) (void)hipEventRecord(ev[2], s);
 }
 
+// Bytes allocated for an arena that has to hold `bytes`.
+size_t arena_want(const bbc_ctx* ctx, size_t bytes) {
+    const size_t want = bytes + bytes / 8 + (1u << 20);
+    return ctx->limit > 0 ? std::min(want, std::max(bytes, (size_t)ctx->limit)) : want;
+}
+
+// Whether the context's arena holds `bytes` or can be made to, by the scratch
+// limit and the memory that is free.
+bool can_grow(const bbc_ctx* ctx, size_t bytes) {
+    if (ctx->limit > 0 && bytes > (size_t)ctx->limit) return false;
+    if (bytes <= ctx->arena_bytes) return true;
+    size_t free = 0, all = 0;
+    return hipMemGetInfo(&free, &all) == hipSuccess && arena_want(ctx, bytes) <= free + ctx->arena_bytes;
+}
+
 bbc_status grow(bbc_ctx* ctx, char** arena, size_t* have, size_t bytes) {
     if (ctx->limit > 0 && bytes > (size_t)ctx->limit)
         return fail(ctx, BBC_ENOMEM, "the call needs " + std::to_string(bytes) + " bytes of scratch, above its "
@@ -630,8 +640,7 @@ bbc_status grow(bbc_ctx* ctx, char** arena, size_t* have, size_t bytes) {
         *arena = nullptr;
         *have = 0;
     }
-    size_t want = bytes + bytes / 8 + (1u << 20);
-    if (ctx->limit > 0 && want > (size_t)ctx->limit) want = (size_t)ctx->limit;  // >= bytes
+    const size_t want = arena_want(ctx, bytes);
     if (hipMalloc((void**)arena, want) != hipSuccess) {
         *arena = nullptr;
         (void)hipGetLastError();
@@ -1014,12 +1023,13 @@ bbc_status run_job(bbc_ctx* ctx, Job& J, const bbc_options& opts, hipStream_t s,
     bbc_status rc = BBC_OK;
     if (J.top || J.mat) {
         // the one-sided walk decides what a scratch limit refuses; it takes
-        // over where the others do not fit
+        // over where the others do not fit, with the arena as it is (freed and
+        // asked for anew on each such call, it would cost more than the walk)
         Job one = J;
         one.top = one.mat = false;
         const size_t need = job_bytes(J);
         const bool refused = ctx->limit > 0 && job_bytes(one) > (size_t)ctx->limit;
-        if (refused || grow(ctx, &ctx->arena, &ctx->arena_bytes, need) != BBC_OK) J.top = J.mat = false;
+        if (refused || !can_grow(ctx, need) || grow(ctx, &ctx->arena, &ctx->arena_bytes, need) != BBC_OK) J.top = J.mat = false;
     }
     if (!J.top && !J.mat) rc = grow(ctx, &ctx->arena, &ctx->arena_bytes, job_bytes(J));
     if (rc != BBC_OK) return rc;

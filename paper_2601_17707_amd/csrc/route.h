@@ -104,6 +104,31 @@ inline bool matrix_pays(const RouteInput& r, MatrixShape* shape) {
     return true;
 }
 
+// log2 of the counter words per band of the count from both sides, at most
+// `words`: narrower bands where a side holds few, so that the bands of the
+// heaviest vertices spread over the chip.
+inline int band_log(int words, int64_t widest_side) {
+    int lw = 0;
+    while ((2 << lw) <= words) ++lw;
+    while (lw > 9 && ((int64_t)16 << lw) > widest_side) --lw;
+    return lw;
+}
+
+// Most entries that the band index of one side's lists (n_a lists, m entries in
+// all) can have, over the bands of the other side's n_b ranks: bands of
+// 2^(lw - 1) to 2^(lw + 2) ranks.  Up to kTopFewBands bands every list that is
+// not empty has an entry per band and one more, beyond that only lists of as
+// many entries as there are bands.
+constexpr int64_t kTopFewBands = 16;
+inline int64_t index_words(int64_t n_a, int64_t n_b, int64_t m, int lw) {
+    const auto bands = [&](int log) { return (n_b + (1ll << log) - 1) >> log; };
+    const int64_t most = bands(lw - 1), least = bands(lw + 2);
+    if (most <= 1) return 0;
+    const int64_t few = least <= kTopFewBands ? (std::min(most, kTopFewBands) + 1) * std::min(n_a, m) : 0;
+    const int64_t many = most > kTopFewBands ? m + m / std::max(kTopFewBands + 1, least) : 0;
+    return std::max(few, many);
+}
+
 // The route of a graph (with kMatrix, its matrix).
 inline Route choose_route(const RouteInput& r, MatrixShape* shape) {
     if (r.blocks) return Route::kOneSided;

@@ -99,7 +99,6 @@ struct TopCounts {
     unsigned int queue_hash[kTopTiers];
 };
 
-constexpr uint32_t kTopFewBands = 16;  // up to this many bands, every list has index entries
 constexpr uint32_t kNoIndex = 0xffffffffu;
 
 // What the walk kernels read.
@@ -117,7 +116,7 @@ struct TopArgs {
 
 // Device buffers of the build.
 struct TopBuild {
-    uint32_t *deg, *key, *inv, *vk_a, *vv_a, *degr, *off, *thr, *kx, *order, *skey, *ioff, *icnt;
+    uint32_t *deg, *key, *inv, *vk_a, *vv_a, *degr, *off, *thr, *kx, *order, *ioff, *icnt;
     int32_t* rank;
     uint32_t *first, *last;
     unsigned long long* work;

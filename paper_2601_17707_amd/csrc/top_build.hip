@@ -197,8 +197,7 @@ __global__ __launch_bounds__(256) void k_top_vertices(const uint32_t* __restrict
 // A list of side A is walked in bands of B ranks: idx[ioff[y] + b] = first
 // position of list y with a rank in band b or above, b = 0 .. nb.  Where there
 // are more than kTopFewBands bands only lists with at least nb entries are
-// indexed (the walk searches the shorter ones), so the index holds at most
-// 2 m + (kTopFewBands + 1) n entries.
+// indexed (the walk searches the shorter ones); index_words bounds the entries.
 
 __global__ void k_top_idx_count(const uint32_t* __restrict__ off, int64_t n_u, int64_t n,
                                 const TopBands* __restrict__ bands, uint32_t* __restrict__ cnt, const DevStatus* st) {
@@ -207,7 +206,7 @@ __global__ void k_top_idx_count(const uint32_t* __restrict__ off, int64_t n_u, i
         uint32_t c = 0;
         if (!bad) {
             const uint32_t len = off[y + 1] - off[y], nb = (uint32_t)bands[y < n_u ? 1 : 0].nb;
-            if (nb > 1 && (len >= nb || (len > 0 && nb <= kTopFewBands))) c = nb + 1;
+            if (nb > 1 && (len >= nb || (len > 0 && nb <= (uint32_t)kTopFewBands))) c = nb + 1;
         }
         cnt[y] = c;
     }

@@ -4,6 +4,7 @@ pipeline."""
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 import test_gpu_one_sided as one_sided
@@ -20,6 +21,11 @@ int main() {
     long long nu, nv, m;
     int au, pv, bl, kn, dup;
     while (std::scanf("%lld %lld %lld %d %d %d %d %d", &nu, &nv, &m, &au, &pv, &bl, &kn, &dup) == 8) {
+        if (pv == 2) {  // au: words of a band
+            const int lw = band_log(au, std::max(nu, nv));
+            std::printf("index %d %lld\n", lw, (long long)index_words(nu, nv, m, lw));
+            continue;
+        }
         MatrixShape s{};
         r = RouteInput{nu, nv, m, au != 0, pv != 0, bl != 0, kn != 0, dup != 0, 256};
         const Route x = choose_route(r, &s);
@@ -38,13 +44,48 @@ def route(tmp_path_factory):
     exe = str(d / "main")
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", exe, str(src)])
 
-    def ask(n_u, n_v, m, side="auto", per_vertex=False, blocks=False, knobs=False, dup=True):
+    def ask(n_u, n_v, m, raw=None, side="auto", per_vertex=False, blocks=False, knobs=False, dup=True):
         au = side == "u" or (side == "auto" and n_u < n_v)
-        line = " ".join(str(int(x)) for x in (n_u, n_v, m, au, per_vertex, blocks, knobs, dup))
+        line = raw or " ".join(str(int(x)) for x in (n_u, n_v, m, au, per_vertex, blocks, knobs, dup))
         out = subprocess.run([exe], input=line + "\n", capture_output=True, text=True, check=True).stdout.split()
+        if raw:
+            return out
         return out[0], tuple(map(int, out[1:]))
 
     return ask
+
+
+def bands(degrees, lw):
+    """Bands of a side's ranks (ascending degree): whole bands of 2^(lw + 2),
+    2^(lw + 1) and 2^lw ranks below the first rank of degree 16, 256 and 65536,
+    then bands of 2^(lw - 1)."""
+    end, at, n = len(degrees), 0, 0
+    for k, d in enumerate((16, 256, 65536, None)):
+        top = end if d is None else int(np.searchsorted(degrees, d))
+        size = 1 << (lw + 2 - k)
+        c = -(-(end - at) // size) if top >= end else (top - at) // size
+        n += c
+        at = min(at + c * size, end)
+    return n
+
+
+@pytest.mark.parametrize("words", [4096, 16384, 32768])
+@pytest.mark.parametrize("seed", range(40))
+def test_index_words(route, words, seed):
+    """The band index never has more entries than it is given room for."""
+    rng = np.random.default_rng(seed)
+    n_a, n_b = (int(x) for x in np.exp(rng.uniform(np.log(3), np.log(300_000), 2)))
+    m = int(np.exp(rng.uniform(np.log(2), np.log(3_000_000))))
+    out = route(n_a, n_b, m, raw=f"{n_a} {n_b} {m} {words} 2 0 0 0")
+    lw, room = map(int, out[1:])
+    p = np.arange(1, n_b + 1) ** rng.uniform(0, 3)
+    deg_b = np.sort(rng.multinomial(m, p / p.sum()))
+    nb = bands(deg_b, lw)
+    # lists of side a: random, all of one length, and as many as the entries of a band each give
+    for lists in (rng.multinomial(m, np.full(n_a, 1 / n_a)), np.full(n_a, m // n_a), np.full(min(n_a, m // nb), nb),
+                  np.ones(min(n_a, m), int)):
+        indexed = (lists >= nb) | ((lists > 0) & (nb <= 16))
+        assert (0 if nb <= 1 else int(indexed.sum()) * (nb + 1)) <= room
 
 
 TOTALS = [
