@@ -271,7 +271,7 @@ typedef struct {
     uint64_t wedges;      /* sum over centres c of C(deg c, 2): the wedges of the anchor side (a count from both
                            * sides walks fewer) */
     uint64_t bands;       /* LDS counter bands processed by the wedge kernel */
-    int32_t grid;         /* persistent workgroups launched */
+    int32_t grid;         /* persistent workgroups launched (matrix products: all workgroups) */
     int32_t block;        /* threads per workgroup */
     float ms_checks;      /* HIP event times on the caller's stream (timing option) */
     float ms_build;       /* degrees, ranks, degree-ordered CSR, schedule */
@@ -281,7 +281,7 @@ typedef struct {
     int32_t n_blocks;
     uint64_t dense_ops;   /* int8 multiply-adds x 2 of the upper-triangle block tiles */
     uint64_t wedges_all;  /* sum over centres of C(deg c, 2), dense blocks included */
-    int32_t band_words;   /* LDS counter band of the wedge kernel, 32-bit words */
+    int32_t band_words;   /* LDS counter band of the wedge kernel, 32-bit words (0: matrix products) */
     int32_t tuned;        /* 1 if the kernel shape came from the tuning table */
     int32_t schedule;     /* BBC_SCHED_* of the wedge kernel */
 } bbc_stats;
@@ -303,7 +303,11 @@ bbc_status bbc_last_stats(const bbc_ctx* ctx, bbc_stats* out);
  * m / n_S), n_S the anchor side of the default side rule.  Later bbc_count
  * and batched calls of the same class use it unless their options fix the
  * shape or set no_tuning (queue_chunk and wave_max_work only when they are
- * 0).  *chosen (host, may be NULL) receives options holding the choice.
+ * 0).  The one-sided walk and the count from both sides are tuned each by its
+ * own times: a graph that is counted from both sides is searched both ways, a
+ * batch by the one-sided walk only, and a call uses the choice of the walk it
+ * takes (matrix products take none).  *chosen (host, may be NULL) receives
+ * options holding the choice for this graph's own calls.
  * Every configuration must give the same count (BBC_EDEVICE otherwise); the
  * count never depends on them.  Errors: as bbc_count. */
 bbc_status bbc_autotune(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges, const int32_t* offsets,
@@ -322,8 +326,9 @@ bbc_status bbc_autotune_batched(bbc_ctx* ctx, int32_t n_graphs, const bbc_graph_
  * line "bbc-tune 3 gfx950", then one line per size class: "ns_bits deg_bits
  * band_words wg_size wg_per_cu schedule queue_chunk wave_max_work
  * min_degree dense_tile ms" (band_words 0: the class has only dense-block
- * choices; queue_chunk, min_degree and dense_tile 0: not tuned).
- * BBC_EINVAL if the file cannot be written. */
+ * choices; queue_chunk, min_degree and dense_tile 0: not tuned).  Of a class
+ * tuned for both walks the line holds the choice made last, and a loaded line
+ * serves both.  BBC_EINVAL if the file cannot be written. */
 bbc_status bbc_tune_save(const bbc_ctx* ctx, const char* path);
 
 /* Reads such a file (or an older one: version 2 lines end after the

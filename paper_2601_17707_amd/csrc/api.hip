@@ -68,6 +68,7 @@ void launch_dense(const DevBlock* blocks, const DevTile* tiles, int32_t n_tiles,
 void launch_matrix_build(const int32_t* off, const int32_t* adj, const int8_t* sg, int32_t n_u, int32_t n_v, int64_t m,
                          int s_is_u, int check_sign, int8_t* mat, int64_t bytes, int64_t kpad, DevStatus* st,
                          hipStream_t s);
+constexpr int kMatrixThreads = 256;
 void launch_matrix_pairs(const int8_t* mat, int32_t n_r, int32_t rpad, int32_t kpad, int tile, DevStatus* st,
                          hipStream_t s);
 void launch_bidx(const uint32_t* ckey, const uint32_t* coff, const uint32_t* packed, int64_t m, int64_t n_c, int gs,
@@ -123,17 +124,25 @@ __global__ __launch_bounds__(kStatusThreads) void k_status_init(DevStatus* st) {
         st->n_light = 0;
     }
 }
-// One entry of the tuning table: the fastest wedge-kernel shape measured
-// for a size class (bit lengths of n_S and of m / n_S).
-struct TuneEntry {
-    int32_t ns_bits, deg_bits;
+// The fastest launch of one walk measured for a size class.
+struct TuneShape {
     int32_t band_words, wg_size, wg_per_cu;  // band_words = 0: shape not tuned
     int32_t schedule;       // BBC_SCHED_*
     int32_t queue_chunk;    // 0: not tuned (1)
     int32_t wave_max_work;  // 0: the shape's largest, -1: no wave regime
+    float ms;
+};
+
+// One entry of the tuning table, a size class (bit lengths of n_S and of
+// m / n_S).  The one-sided walk and the count from both sides are different
+// kernels: each has its own shape, timed on it.  A file holds one shape per
+// class, the one tuned last, and loading it sets both.
+struct TuneEntry {
+    int32_t ns_bits, deg_bits;
+    TuneShape shape[2];     // [0] the one-sided walk, [1] from both sides
+    int32_t last;           // which of them was tuned last
     int32_t min_degree;     // planner threshold; 0: not tuned (256)
     int32_t dense_tile;     // int8 matrix tile; 0: not tuned (128)
-    float ms;
 };
 }  // namespace bbc
 
@@ -752,18 +761,19 @@ const TuneEntry* tune_find(const bbc_ctx* ctx, int64_t n_s, int64_t m) {
 // shape, grid and schedule (when none of them is fixed), the queue chunk
 // and wave-regime threshold (when 0) and the dense tile (when 0).  Returns
 // whether the shape came from the table.
-bool apply_tuning(const bbc_ctx* ctx, bbc_options& o, int64_t n_s, int64_t m, bool full) {
-    if (o.no_tuning || full) return false;
+bool apply_tuning(const bbc_ctx* ctx, bbc_options& o, int64_t n_s, int64_t m, bool full, Route route) {
+    if (o.no_tuning || full || route == Route::kMatrix) return false;
     const TuneEntry* e = tune_find(ctx, n_s, m);
     if (!e) return false;
+    const TuneShape& t = e->shape[route == Route::kTwoSided];
     if (o.dense_tile == 0) o.dense_tile = e->dense_tile;
-    if (o.band_words || o.wg_size || o.wg_per_cu || o.schedule || e->band_words == 0) return false;
-    o.band_words = e->band_words;
-    o.wg_size = e->wg_size;
-    o.wg_per_cu = e->wg_per_cu;
-    o.schedule = e->schedule;
-    if (o.queue_chunk == 0) o.queue_chunk = e->queue_chunk;
-    if (o.wave_max_work == 0) o.wave_max_work = e->wave_max_work;
+    if (o.band_words || o.wg_size || o.wg_per_cu || o.schedule || t.band_words == 0) return false;
+    o.band_words = t.band_words;
+    o.wg_size = t.wg_size;
+    o.wg_per_cu = t.wg_per_cu;
+    o.schedule = t.schedule;
+    if (o.queue_chunk == 0) o.queue_chunk = t.queue_chunk;
+    if (o.wave_max_work == 0) o.wave_max_work = t.wave_max_work;
     return true;
 }
 
@@ -782,7 +792,10 @@ TuneEntry& tune_slot(bbc_ctx* ctx, int64_t n_s, int64_t m) {
     tune_class(n_s, m, &a, &b);
     for (TuneEntry& x : ctx->tune)
         if (x.ns_bits == a && x.deg_bits == b) return x;
-    ctx->tune.push_back(TuneEntry{a, b, 0, 0, 0, 0, 0, 0, 0, 0, 0.f});
+    TuneEntry e{};
+    e.ns_bits = a;
+    e.deg_bits = b;
+    ctx->tune.push_back(e);
     return ctx->tune.back();
 }
 
@@ -838,7 +851,7 @@ bbc_status batch_job(bbc_ctx* ctx, int32_t n_graphs, const bbc_graph_desc* d, co
     J.n_s = ns;
     J.n_c = nc;
     J.checks = o.checks;
-    J.tuned = apply_tuning(ctx, o, ns, m, false);
+    J.tuned = apply_tuning(ctx, o, ns, m, false, Route::kOneSided);
     J.band_words = o.band_words;
     J.schedule = o.schedule;
     J.wg_size = o.wg_size;
@@ -947,9 +960,10 @@ void fill_stats(bbc_ctx* ctx, const Job& J, const DevStatus& h, int block) {
     S.bands = h.bands;
     S.n_blocks = J.n_blocks;
     S.dense_ops = J.dense_ops;
-    S.grid = J.top ? J.top_grid : J.grid;
+    const int tiles = J.mat ? J.mat_shape.rpad / J.mat_shape.tile : 0;
+    S.grid = J.mat ? tiles * tiles : J.top ? J.top_grid : J.grid;
     S.block = block;
-    S.band_words = J.top ? J.top_words : wedge_band(J.band_words, J.wg_size, J.pv != nullptr);
+    S.band_words = J.mat ? 0 : J.top ? J.top_words : wedge_band(J.band_words, J.wg_size, J.pv != nullptr);
     S.tuned = J.tuned ? 1 : 0;
     S.schedule = J.schedule;
 }
@@ -1010,7 +1024,7 @@ bbc_status run_planned(bbc_ctx* ctx, const Job& J, char* arena, const bbc_option
     fold_sums(*ctx->st_host);
     const bbc_status rc = status_result(ctx, *ctx->st_host);
     if (rc != BBC_OK) return rc;
-    fill_stats(ctx, J, *ctx->st_host, J.top ? J.top_wg : wedge_block(J.band_words, J.wg_size, J.pv != nullptr));
+    fill_stats(ctx, J, *ctx->st_host, J.mat ? kMatrixThreads : J.top ? J.top_wg : wedge_block(J.band_words, J.wg_size, J.pv != nullptr));
     return timing ? timed_stats(ctx) : BBC_OK;
 }
 
@@ -1050,8 +1064,10 @@ bbc_status run_job(bbc_ctx* ctx, Job& J, const bbc_options& opts, hipStream_t s,
 // and grid with both schedules x queue_chunk in {1, 2, 4, 8, 16} x
 // wave_max_work in {shape's largest, 256, off}.  Each configuration runs reps + 1 times (the first warms up);
 // its score is the best HIP-event time of the wedge kernel.
-template <class Run>
-bbc_status tune_wedge(bbc_ctx* ctx, int32_t reps, Run run, TuneEntry& best) {
+// occ(band_words, wg_size): workgroups of the tuned kernel that fit a CU;
+// *result: the result of every run.
+template <class Run, class Occ>
+bbc_status tune_wedge(bbc_ctx* ctx, int32_t reps, Run run, Occ occ_of, TuneShape& best, uint64_t* result) {
     if (reps <= 0) reps = 2;
     uint64_t first = 0;
     bool counted = false, have = false;
@@ -1078,7 +1094,7 @@ bbc_status tune_wedge(bbc_ctx* ctx, int32_t reps, Run run, TuneEntry& best) {
     for (int i = 0; i < n_shapes; ++i) {
         int wg, bw;
         wedge_shape(i, &wg, &bw);
-        const int occ = wedge_blocks_per_cu(bw, wg, false);
+        const int occ = occ_of(bw, wg);
         for (int cfg = 0; cfg < 2 * occ; ++cfg) {
             const int wpc = cfg / 2 + 1, sched = cfg & 1;  // both schedules at each grid
             if (wpc > 2 && wpc < occ) continue;           // 1, 2 and as many as fit
@@ -1092,12 +1108,12 @@ bbc_status tune_wedge(bbc_ctx* ctx, int32_t reps, Run run, TuneEntry& best) {
             const bbc_status rc = time_cfg(o, &ms);
             if (rc != BBC_OK) return rc;
             if (!have || ms < best.ms) {
-                best = TuneEntry{0, 0, bw, wg, wpc, sched, 1, 0, 0, 0, ms};
+                best = TuneShape{bw, wg, wpc, sched, 1, 0, ms};
                 have = true;
             }
         }
     }
-    const TuneEntry shape = best;
+    const TuneShape shape = best;
     // both schedules again: the best chunk can change which one wins
     for (const int32_t sched : {BBC_SCHED_DYNAMIC, BBC_SCHED_STATIC})
         for (const int32_t qc : {1, 2, 4, 8, 16})
@@ -1121,20 +1137,16 @@ bbc_status tune_wedge(bbc_ctx* ctx, int32_t reps, Run run, TuneEntry& best) {
                     best.ms = ms;
                 }
             }
+    *result = first;
     return BBC_OK;
 }
 
-// Records a wedge-kernel tuning result under the size class (keeping the
-// class's dense-block fields) and reports it in *chosen (may be null).
-void tune_keep(bbc_ctx* ctx, int64_t n_s, int64_t m, const TuneEntry& best, bbc_options* chosen) {
+// Records a walk's tuning result under the size class (keeping the class's
+// other fields) and reports it in *chosen (may be null).
+void tune_keep(bbc_ctx* ctx, int64_t n_s, int64_t m, int walk, const TuneShape& best, bbc_options* chosen) {
     TuneEntry& e = tune_slot(ctx, n_s, m);
-    e.band_words = best.band_words;
-    e.wg_size = best.wg_size;
-    e.wg_per_cu = best.wg_per_cu;
-    e.schedule = best.schedule;
-    e.queue_chunk = best.queue_chunk;
-    e.wave_max_work = best.wave_max_work;
-    e.ms = best.ms;
+    e.shape[walk] = best;
+    e.last = walk;
     if (chosen) {
         bbc_options_init(chosen);
         chosen->band_words = best.band_words;
@@ -1192,10 +1204,11 @@ bbc_status count_classes(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges
 
 // bbc_count and bbc_count_noalloc: the same pipeline, its buffers carved
 // from the context's arena (grown on demand) or from the device's fixed
-// scratch (no allocation; sizes beyond it are rejected).
+// scratch (no allocation; sizes beyond it are rejected).  one_sided: by the
+// one-sided walk (the autotuner).
 bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges, const int32_t* offsets,
                         const int32_t* adj, const int8_t* signs, uint64_t* total, uint64_t* per_vertex,
-                        const bbc_options* opts_in, void* stream, bool fixed) {
+                        const bbc_options* opts_in, void* stream, bool fixed, bool one_sided = false) {
     if (!ctx) return BBC_EINVAL;
     ctx->err.clear();
     bbc_options opts;
@@ -1229,7 +1242,10 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
     const bool full = per_vertex != nullptr;
     const bool open = !(opts.band_words || opts.wg_size || opts.wg_per_cu || opts.schedule || opts.queue_chunk ||
                         opts.wave_max_work);  // no knob of the walk is set
-    J.tuned = apply_tuning(ctx, opts, J.n_s, n_edges, full);
+    RouteInput in{n_u, n_v, n_edges, J.s_is_u, full, opts.n_blocks > 0, !open,
+                  (opts.checks & BBC_CHECK_DUPLICATES) != 0, ctx->n_cu};
+    const Route route = one_sided ? Route::kOneSided : choose_route(in, &J.mat_shape);
+    J.tuned = apply_tuning(ctx, opts, J.n_s, n_edges, full, route);
     J.band_words = opts.band_words;
     J.schedule = opts.schedule;
     J.wg_size = opts.wg_size;
@@ -1243,9 +1259,6 @@ bbc_status count_single(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges,
         rc = block_job(ctx, opts, J, db, dt);
         if (rc != BBC_OK) return rc;
     }
-    RouteInput in{n_u, n_v, n_edges, J.s_is_u, full, opts.n_blocks > 0, !open,
-                  (opts.checks & BBC_CHECK_DUPLICATES) != 0, ctx->n_cu};
-    const Route route = choose_route(in, &J.mat_shape);
     J.mat = route == Route::kMatrix;
     if (route == Route::kTwoSided) set_top(ctx, J, opts);
     if (fixed) {
@@ -1702,14 +1715,24 @@ bbc_status bbc_batch_wait(bbc_batch_plan* p, void* stream) {
 bbc_status bbc_autotune(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n_edges, const int32_t* offsets,
                         const int32_t* adj, const int8_t* signs, int32_t reps, bbc_options* chosen, void* stream) {
     if (!ctx) return BBC_EINVAL;
-    TuneEntry best{};
-    auto run = [&](const bbc_options& o, uint64_t* res) {
-        return bbc_count(ctx, n_u, n_v, n_edges, offsets, adj, signs, res, nullptr, &o, stream);
-    };
-    bbc_status rc = tune_wedge(ctx, reps, run, best);
-    if (rc != BBC_OK) return rc;
     const bool su = side_is_u(BBC_SIDE_AUTO, n_u, n_v);
-    tune_keep(ctx, su ? n_u : n_v, n_edges, best, chosen);
+    MatrixShape none;
+    const bool two = n_u >= 0 && n_v >= 0 &&
+                     choose_route({n_u, n_v, n_edges, su, false, false, true, true, ctx->n_cu}, &none) == Route::kTwoSided;
+    TuneShape best[2] = {};
+    uint64_t res[2] = {0, 0};
+    for (int walk = 0; walk <= (two ? 1 : 0); ++walk) {
+        auto run = [&](const bbc_options& o, uint64_t* r) {
+            return count_single(ctx, n_u, n_v, n_edges, offsets, adj, signs, r, nullptr, &o, stream, false, walk == 0);
+        };
+        auto occ = [&](int bw, int wg) { return walk ? top_blocks_per_cu(bw, wg) : wedge_blocks_per_cu(bw, wg, false); };
+        const bbc_status rc = tune_wedge(ctx, reps, run, occ, best[walk], &res[walk]);
+        if (rc != BBC_OK) return rc;
+    }
+    if (two && res[0] != res[1]) return fail(ctx, BBC_EDEVICE, "autotune: configurations disagree on the result");
+    const int64_t n_s = su ? n_u : n_v;
+    tune_keep(ctx, n_s, n_edges, 0, best[0], chosen);
+    if (two) tune_keep(ctx, n_s, n_edges, 1, best[1], chosen);  // the walk of the graph's own calls: reported and saved
     return BBC_OK;
 }
 
@@ -1731,15 +1754,17 @@ bbc_status bbc_autotune_batched(bbc_ctx* ctx, int32_t n_graphs, const bbc_graph_
         *res = h;
         return BBC_OK;
     };
-    TuneEntry best{};
-    bbc_status rc = tune_wedge(ctx, reps, run, best);
+    TuneShape best{};
+    uint64_t res = 0;
+    bbc_status rc = tune_wedge(ctx, reps, run, [](int bw, int wg) { return wedge_blocks_per_cu(bw, wg, false); }, best,
+                               &res);
     if (rc != BBC_OK) return rc;
     int64_t ns = 0, m = 0;
     for (int32_t g = 0; g < n_graphs; ++g) {
         m += descs[g].n_edges;
         ns += side_is_u(BBC_SIDE_AUTO, descs[g].n_u, descs[g].n_v) ? descs[g].n_u : descs[g].n_v;
     }
-    tune_keep(ctx, ns, m, best, chosen);
+    tune_keep(ctx, ns, m, 0, best, chosen);
     return BBC_OK;
 }
 
@@ -1817,7 +1842,7 @@ bbc_status bbc_autotune_blocks(bbc_ctx* ctx, int32_t n_u, int32_t n_v, int64_t n
     TuneEntry& e = tune_slot(ctx, su ? n_u : n_v, n_edges);
     e.min_degree = best_tau;
     e.dense_tile = best_tile;
-    if (e.band_words == 0) e.ms = (float)best_ms;
+    if (e.shape[e.last].band_words == 0) e.shape[e.last].ms = (float)best_ms;
     if (chosen_plan) {
         bbc_plan_options_init(chosen_plan);
         chosen_plan->min_degree = best_tau;
@@ -1997,10 +2022,12 @@ bbc_status bbc_tune_save(const bbc_ctx* ctx, const char* path) {
     FILE* f = fopen(path, "w");
     if (!f) return fail(const_cast<bbc_ctx*>(ctx), BBC_EINVAL, std::string("cannot write ") + path);
     bool ok = fprintf(f, "bbc-tune 3 gfx950\n") > 0;
-    for (const TuneEntry& e : ctx->tune)
-        ok = ok && fprintf(f, "%d %d %d %d %d %d %d %d %d %d %.4f\n", e.ns_bits, e.deg_bits, e.band_words, e.wg_size,
-                           e.wg_per_cu, e.schedule, e.queue_chunk, e.wave_max_work, e.min_degree, e.dense_tile,
-                           (double)e.ms) > 0;
+    for (const TuneEntry& e : ctx->tune) {
+        const TuneShape& t = e.shape[e.last];
+        ok = ok && fprintf(f, "%d %d %d %d %d %d %d %d %d %d %.4f\n", e.ns_bits, e.deg_bits, t.band_words, t.wg_size,
+                           t.wg_per_cu, t.schedule, t.queue_chunk, t.wave_max_work, e.min_degree, e.dense_tile,
+                           (double)t.ms) > 0;
+    }
     ok = (fclose(f) == 0) && ok;
     return ok ? BBC_OK : fail(const_cast<bbc_ctx*>(ctx), BBC_EINVAL, std::string("write failed: ") + path);
 }
@@ -2027,13 +2054,14 @@ bbc_status bbc_tune_load(bbc_ctx* ctx, const char* path) {
             continue;
         }
         TuneEntry e{};
-        e.schedule = BBC_SCHED_DYNAMIC;
+        TuneShape& t = e.shape[0];
+        t.schedule = BBC_SCHED_DYNAMIC;
         double ms = 0;
         // whitespace-separated fields: integers, then the time; every field
         // must parse in full
         const int want = version == 1 ? 6 : version == 2 ? 7 : 11;
-        int32_t* ints[10] = {&e.ns_bits,  &e.deg_bits,    &e.band_words,    &e.wg_size,    &e.wg_per_cu,
-                             &e.schedule, &e.queue_chunk, &e.wave_max_work, &e.min_degree, &e.dense_tile};
+        int32_t* ints[10] = {&e.ns_bits,  &e.deg_bits,    &t.band_words,    &t.wg_size,    &t.wg_per_cu,
+                             &t.schedule, &t.queue_chunk, &t.wave_max_work, &e.min_degree, &e.dense_tile};
         if (version == 1) ints[5] = nullptr;  // no schedule column: the time follows wg_per_cu
         int n = 0;
         bool good = true;
@@ -2049,18 +2077,19 @@ bbc_status bbc_tune_load(bbc_ctx* ctx, const char* path) {
                 good = good && *end == 0;
             }
         }
-        if (version == 1) e.schedule = BBC_SCHED_DYNAMIC;
-        const bool shape_ok = e.band_words == 0 ? (version == 3 && e.wg_size == 0 && e.wg_per_cu == 0)
-                                                : (e.wg_size > 0 && wedge_shape_ok(e.band_words, e.wg_size));
+        if (version == 1) t.schedule = BBC_SCHED_DYNAMIC;
+        const bool shape_ok = t.band_words == 0 ? (version == 3 && t.wg_size == 0 && t.wg_per_cu == 0)
+                                                : (t.wg_size > 0 && wedge_shape_ok(t.band_words, t.wg_size));
         if (!good || n != want || e.ns_bits < 0 || e.ns_bits > 64 || e.deg_bits < 0 || e.deg_bits > 64 ||
-            e.wg_per_cu < 0 || e.band_words < 0 || !shape_ok ||
-            (e.schedule != BBC_SCHED_DYNAMIC && e.schedule != BBC_SCHED_STATIC) || e.queue_chunk < 0 ||
-            e.queue_chunk > 65536 || e.wave_max_work < -1 || e.min_degree < 0 ||
+            t.wg_per_cu < 0 || t.band_words < 0 || !shape_ok ||
+            (t.schedule != BBC_SCHED_DYNAMIC && t.schedule != BBC_SCHED_STATIC) || t.queue_chunk < 0 ||
+            t.queue_chunk > 65536 || t.wave_max_work < -1 || e.min_degree < 0 ||
             (e.dense_tile != 0 && e.dense_tile != 64 && e.dense_tile != 128)) {
             rc = fail(ctx, BBC_EINVAL, std::string(path) + ":" + std::to_string(ln) + ": malformed tuning entry");
             break;
         }
-        e.ms = (float)ms;
+        t.ms = (float)ms;
+        e.shape[1] = t;
         got.push_back(e);
     }
     if (rc == BBC_OK && ln == 0) rc = fail(ctx, BBC_EINVAL, std::string(path) + ": empty file");
