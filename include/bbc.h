@@ -270,7 +270,7 @@ typedef struct {
     int64_t n_edges;
     uint64_t wedges;      /* sum over centres c of C(deg c, 2): the wedges of the anchor side (a count from both
                            * sides walks fewer) */
-    uint64_t bands;       /* LDS counter bands processed by the wedge kernel */
+    uint64_t bands;       /* LDS counter bands processed (hashed anchors and matrix products take none) */
     int32_t grid;         /* persistent workgroups launched (matrix products: all workgroups) */
     int32_t block;        /* threads per workgroup */
     float ms_checks;      /* HIP event times on the caller's stream (timing option) */

@@ -1036,7 +1036,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
         for (int i = tid; i < (1 << lt) / 4; i += WG) t4[i] = uint4{0u, 0u, 0u, 0u};
     };
     __syncthreads();
-    unsigned long long acc = 0, n_done = 0;
+    unsigned long long acc = 0;
     Mid m;
     bool has = false;
     {
@@ -1100,7 +1100,6 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
         unsigned long long mine = bad ? 0ull : 2ull * s;
         if (bad && tid == 0) a.extra[atomicAdd(&a.tc->n_extra, 1u)] = t.lo;
         clear(t.mode);
-        ++n_done;
         acc += mine;
         __syncthreads();
         if (bad) {  // the same for every thread
@@ -1108,7 +1107,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_hash(TopArgs a, int tier) {
             __syncthreads();
         }
     }
-    add_total<WG>(a, sh, acc, n_done);
+    add_total<WG>(a, sh, acc, 0);
 }
 
 // ------------------------------------------------------------ wave regime
