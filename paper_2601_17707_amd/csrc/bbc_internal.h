@@ -239,8 +239,9 @@ void radix_sort(const uint32_t* k_in, uint32_t* k_a, uint32_t* k_b, const uint32
                 const uint32_t** v0_out, const uint32_t** v1_out, int32_t* inv_out = nullptr);
 
 // The same sort with every destination named: stable, on bits
-// [shift0, shift0 + bits) of the keys, radix_passes(bits, n) passes going through a, b, a, ... and the last one to `out`, which may
-// share memory with whichever of the inputs, a or b that pass does not read.
+// [shift0, shift0 + bits) of the keys, radix_passes(bits, n) passes going
+// through a, b, a, ... and the last one to `out`, which may share memory with
+// whichever of the inputs, a or b that pass does not read.
 // With v1_iota payload 1 is iota0 + the input index; out.v1 may be NULL when
 // inv_out is given.
 struct SortBufs {

@@ -159,8 +159,10 @@ size_t radix_hist_size(int64_t n) { return (size_t)256 * (size_t)((n + kRsTile -
 // copy on large sorts), so digits of 9 or 10 bits are taken where they save a
 // pass: 17 to 20 bits in two passes, 25 to 30 in three.  20M items with 20-bit
 // keys: 230 us a pass of 10 bits and 150 us of 8, their histograms and scans
-// 45 and 40 us; 2M items with 17-bit keys: 33 and 22 us a pass.  Below kRsWideMin items their histograms (512 or 1024 counts
-// per tile of 8704 or 17408) would exceed radix_hist_size.
+// 45 and 40 us; 2M items with 17-bit keys: 33 and 22 us a pass; 100M items with
+// 17-bit keys: 1262 us in two passes of 9 bits and 1753 in three of 8.  Below
+// kRsWideMin items their histograms (512 or 1024 counts per tile of 8704 or
+// 17408) would exceed radix_hist_size.
 constexpr int64_t kRsWideMin = 278528;
 static int radix_digit(int bits, int64_t n) {
     const int p8 = (bits + 7) / 8, p10 = (bits + 9) / 10;
@@ -238,10 +240,10 @@ __global__ __launch_bounds__(RsShape<DB>::kThreads) void k_rs_hist(const uint32_
 // runs of consecutive positions.  Each wave owns consecutive items of the
 // tile, visited in rounds of 64, so the input order is (wave, round, lane).
 // Within a round the lanes that share a digit are found with a ballot per
-// bit; an item's place among its wave's
-// items of that digit is the wave's running count of the digit plus the
-// number of such lanes below it (the lowest of them then advances the
-// count; a wave's LDS operations complete in order).  After one barrier
+// bit; an item's place among its wave's items of that digit is the wave's
+// running count of the digit plus the number of such lanes below it (the
+// lowest of them then advances the count; a wave's LDS operations complete in
+// order).  After one barrier
 // every digit's places are offset by the counts of the waves before.  The
 // key, then each payload, goes to its place in the tile sorted by digit
 // (one LDS buffer, reused) and is written out in order, every digit's run
@@ -388,7 +390,8 @@ __global__ __launch_bounds__(RsShape<DB>::kThreads) void k_rs_scatter(const uint
 // (wave, round, lane) order the ranking uses, so each pass is stable as in
 // k_rs_scatter.  Used for the small sorts (per-anchor keys of small graphs),
 // where the launches of the multi-tile passes would dominate.
-// Sixteen waves of four rounds (13.5 us as four of sixteen, 9.3 us so, 1980 items of 8 bits).
+// Sixteen waves of four rounds (13.5 us as four of sixteen, 9.3 us so, 1980
+// items of 8 bits).
 __global__ __launch_bounds__(kRsOneThreads) void k_rs_single(const uint32_t* keys, uint32_t* keys_out,
                                                           const uint32_t* v0, uint32_t* v0_out, const uint32_t* v1,
                                                           uint32_t* v1_out, int v1_iota, uint32_t iota0,

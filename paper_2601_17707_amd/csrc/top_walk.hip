@@ -321,11 +321,9 @@ __device__ __forceinline__ uint32_t list_seek(const uint32_t* __restrict__ ent, 
     return lo;
 }
 
-// A range of bands [b0, b1) of one anchor (b0 < 0: not on band bounds): ranks
-// [lo, hi); first / last: it starts at the side's first rank / ends at the
-// anchor.
+// The ranks of a band [lo, hi) below an anchor; first / last: it starts at the
+// side's first rank / ends at the anchor.
 struct TopRange {
-    int32_t b0, b1;
     uint32_t lo, hi;
     bool first, last;
 };
@@ -348,14 +346,12 @@ __device__ __forceinline__ unsigned long long reduce_words(uint32_t* __restrict_
     return ps.take();
 }
 
-__device__ __forceinline__ TopRange make_range(const TopBands& B, int32_t b0, int32_t b1, int32_t nbx, int32_t r) {
+__device__ __forceinline__ TopRange make_range(const TopBands& B, int32_t b, int32_t nbx, int32_t r) {
     TopRange rg;
-    rg.b0 = b0;
-    rg.b1 = b1;
-    rg.first = b0 == 0;
-    rg.last = b1 >= nbx;
-    rg.lo = (uint32_t)band_lo(B, b0);
-    rg.hi = rg.last ? (uint32_t)r : (uint32_t)band_lo(B, b1);
+    rg.first = b == 0;
+    rg.last = b + 1 >= nbx;
+    rg.lo = (uint32_t)band_lo(B, b);
+    rg.hi = rg.last ? (uint32_t)r : (uint32_t)band_lo(B, b + 1);
     return rg;
 }
 
@@ -391,16 +387,18 @@ __device__ __forceinline__ void add_total(const TopArgs& a, Shared& sh, unsigned
 // One band of one of the heaviest anchors per task.  A hub's middles are
 // mostly vertices of low degree whose slice of a band holds a few entries or
 // none, so what bounds a band is the latency of reading the middles, not the
-// wedges: a lane takes two consecutive middles there, and the first chunk of the next task is read while the
-// current band is reduced.  The highest middles, whose slices hold thousands,
-// go first and in small chunks, so that no wave is left alone with one.
+// wedges: a lane takes two consecutive middles there, and the first chunk of
+// the next task is read while the current band is reduced.  The highest
+// middles, whose slices hold thousands, go first and in small chunks, so that
+// no wave is left alone with one.
 
 // Middles per lane in the chunks of the lowest ones.
 constexpr int kLaneMids = 2;
 
 // Chunk layout: places from the top, in three sections of chunks of `size`
-// middles (at most 64, a middle per lane), then chunks of kLaneMids per lane.  Anchors of many wedges split their highest middles, whose slices of
-// one band hold thousands each, further.
+// middles (at most 64, a middle per lane), then chunks of kLaneMids per lane.
+// Anchors of many wedges split their highest middles, whose slices of one band
+// hold thousands each, further.
 struct ChunkLayout {
     uint32_t c1, c2, c3;     // first chunk of sections 1, 2 and of the rest
     uint32_t s0, s1, s2;     // middles per chunk
@@ -900,7 +898,7 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
             const TopAnchor x = top_anchor(a, id);
             const int32_t b = (int32_t)(nb_max - 1u - (uint32_t)(nq == 1u ? i / n_all : i % nb_max));
             if (b >= x.nbx) continue;
-            const TopRange rg = make_range(x.B, b, b + 1, x.nbx, x.r);
+            const TopRange rg = make_range(x.B, b, x.nbx, x.r);
             t = TopTask{x.a0,  x.k, (uint32_t)x.r,         rg.lo, rg.hi, 1u << x.B.lw,
                         b,     band_mode(x.B, b), id, (rg.first ? 1u : 0u) | (rg.last ? 2u : 0u) | (a.work[id] >= kFineWork ? 4u : 0u)};
             return;
@@ -959,12 +957,13 @@ __global__ __launch_bounds__(WG, 4) void k_top_bands(TopArgs a) {
 // ------------------------------------------------------- hashed workgroups
 //
 // Anchors of the middle of the range: one anchor per task and workgroup, all
-// its wedges in one hashed table of at least twice as many slots, so the cost follows the wedges and not the ranks below the anchor
-// (in bands they held a few dozen wedges each), and slices need no index: a
-// middle's wedges are its whole prefix.  Chunks of CH middles, highest first,
-// go to the waves in turn; the next anchor is read while this one's table is
-// cleared.  An anchor with a counter past its width is left to the bands (kernel
-// k_top_bands runs after this one).
+// its wedges in one hashed table of at least twice as many slots, so the cost
+// follows the wedges and not the ranks below the anchor (in bands they held a
+// few dozen wedges each), and slices need no index: a middle's wedges are its
+// whole prefix.  Chunks of CH middles, highest first, go to the waves in turn;
+// the next anchor is read while this one's table is cleared.  An anchor with a
+// counter past its width is left to the bands (kernel k_top_bands runs after
+// this one).
 template <int WG, int LTMAX, bool FULL>
 struct HashShared {
     alignas(16) uint32_t tab[1 << LTMAX];

@@ -26,8 +26,8 @@
 //     that rank-sorted lists do not pile onto a few LDS banks;
 //   - the first increment of a counter word sets a bit in an LDS bitmap, so
 //     the reduction only visits touched words;
-//   - sums stay in registers across tasks and are reduced once per wave at
-//     exit (one 64-bit atomic per wave).
+//   - sums stay in registers across tasks and are reduced once per workgroup
+//     at exit (one 64-bit atomic on one of kSumSlots copies).
 //
 // Per-vertex mode (FULL): every anchor walks its whole 2-hop range (endpoints
 // ranked above and below it), so cnt[u] = sum over w != u of
