@@ -8,8 +8,9 @@ on both sides, largest expected degree 50,000, P(-) = 0.2), seed 1.
 
 Prints one JSON line.  value = wedges/s, where the wedges are
 sum over centres c of C(deg c, 2): every wedge u - c - w with w ranked above
-u (the count from both sides covers them by walking fewer; the roofline uses
-the wedges it does walk).  The line also carries the batched measurement
+u (the count from both sides covers them by walking fewer, so value is not a
+rate of wedges walked there: wedges_walked and kernel_wedges_walked_per_s, and
+the roofline, use the wedges it does walk).  The line also carries the batched measurement
 (graphs/s of 10,000 graphs of uneven size, one captured batch plan, against
 a loop of plain per-graph calls), the six sign-pattern classes on the same
 graph, balanced (2,k)-bicliques for k = 2..4 on it, batches of 1,000 and
@@ -47,8 +48,8 @@ INT8_PEAK_TOPS = 5000.0  # MI355X dense int8 matrix throughput, 5.0 POPS
 # Valid only for the kernel sources it was taken on: the bench reports null
 # once their hash differs.
 KERNEL_SOURCES = ["paper_2601_17707_amd/csrc/" + f for f in ("top_walk.hip", "top.h", "band.h", "bbc_internal.h")]
-MEASURED_TRAFFIC = dict(kernel="k_top_bands + k_top_hash + k_top_light", workload=WORKLOAD, bytes=27833814240,
-                        sources_sha256="b1b25222b483efc61d96af87ee1595054e3cde02a458039a322ebd80f524ff02",
+MEASURED_TRAFFIC = dict(kernel="k_top_bands + k_top_hash + k_top_light", workload=WORKLOAD, bytes=27826566368,
+                        sources_sha256="e7df91d8f2e7ee63d0d356119757118afee38d80aaef9fef632e293386f36e5f",
                         summary="profiles/k_top_powerlaw-1m-500k-20m_pmc.md")
 
 
@@ -87,11 +88,11 @@ def two_sided_wedges(g) -> int:
     return int(sum(((d * (d - 1) - p * (p - 1)) // 2).sum() for d, p in ((d_u, p_u), (d_v, p_v))))
 
 
-def two_sided_bytes(g) -> int:
+def two_sided_bytes(g, walked: int) -> int:
     """Bytes the two-sided walk must move: one 4-byte list entry per wedge it
     walks, 16 bytes per middle (entry, end of its wedges, list start, index
     row; every edge is one) and 12 per vertex (schedule entry, list range)."""
-    return 4 * two_sided_wedges(g) + 16 * int(g.m) + 12 * (g.n_u + g.n_v)
+    return 4 * walked + 16 * int(g.m) + 12 * (g.n_u + g.n_v)
 
 
 def algorithmic_bytes(stats: dict) -> int:
@@ -596,7 +597,8 @@ def main():
     wedges = int(st["wedges"])
     kavg = sum(kern_ms) / len(kern_ms)
     two_sided = max(g.n_u, g.n_v) <= 8 * min(g.n_u, g.n_v) and g.m ** 2 <= 64 ** 2 * g.n_u * g.n_v
-    nbytes = two_sided_bytes(g) if two_sided else algorithmic_bytes(st)
+    walked = two_sided_wedges(g) if two_sided else wedges
+    nbytes = two_sided_bytes(g, walked) if two_sided else algorithmic_bytes(st)
     achieved = nbytes / (kavg / 1e3) / 1e9
 
     line = dict(
@@ -619,6 +621,8 @@ def main():
         kernel_ms=kavg,
         build_ms=sum(build_ms) / len(build_ms),
         kernel_wedges_per_s=wedges / (kavg / 1e3) / 1e9,
+        wedges_walked=walked,
+        kernel_wedges_walked_per_s=walked / (kavg / 1e3) / 1e9,
         tuned=tuned,
         tune_s=tune_s,
         ms_per_step_untuned=ms_untuned,
