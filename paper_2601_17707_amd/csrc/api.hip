@@ -636,7 +636,11 @@ bool can_grow(const bbc_ctx* ctx, size_t bytes) {
     if (ctx->limit > 0 && bytes > (size_t)ctx->limit) return false;
     if (bytes <= ctx->arena_bytes) return true;
     size_t free = 0, all = 0;
-    return hipMemGetInfo(&free, &all) == hipSuccess && arena_want(ctx, bytes) <= free + ctx->arena_bytes;
+    if (hipMemGetInfo(&free, &all) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return arena_want(ctx, bytes) <= free + ctx->arena_bytes;
 }
 
 bbc_status grow(bbc_ctx* ctx, char** arena, size_t* have, size_t bytes) {
